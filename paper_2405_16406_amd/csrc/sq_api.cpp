@@ -258,7 +258,7 @@ sq_status sq_w4a4_linear(const uint8_t* xq, const float* x_alpha, const float* x
   g.y = static_cast<uint16_t*>(y);
   g.ldy = ldy;
   g.dbg_acc = dbg_acc;
-  return hip_status(sq::launch_w4a4_gemm(g, static_cast<hipStream_t>(stream)), "w4a4_linear launch");
+  return hip_status(sq::launch_gemm(g, static_cast<hipStream_t>(stream)), "w4a4_linear launch");
 }
 
 sq_status sq_w4a8_linear(const uint8_t* xq, const float* x_alpha, const float* x_beta, int64_t M,
@@ -298,7 +298,8 @@ sq_status sq_w4a8_linear(const uint8_t* xq, const float* x_alpha, const float* x
   g.y = static_cast<uint16_t*>(y);
   g.ldy = ldy;
   g.dbg_acc = dbg_acc;
-  return hip_status(sq::launch_w4a8_gemm(g, static_cast<hipStream_t>(stream)), "w4a8_linear launch");
+  g.a8 = 1;
+  return hip_status(sq::launch_gemm(g, static_cast<hipStream_t>(stream)), "w4a8_linear launch");
 }
 
 sq_status sq_w4a4_linear_swiglu(const uint8_t* xq, const float* x_alpha, const float* x_beta, int64_t M,
@@ -339,7 +340,7 @@ sq_status sq_w4a4_linear_swiglu(const uint8_t* xq, const float* x_alpha, const f
   g.ldy = ldh;
   g.dbg_acc = nullptr;
   g.swiglu = 1;
-  const hipError_t e = sq::launch_w4a4_gemm(g, static_cast<hipStream_t>(stream));
+  const hipError_t e = sq::launch_gemm(g, static_cast<hipStream_t>(stream));
   if (e == hipErrorNotSupported)
     return fail(SQ_ERR_UNSUPPORTED, "M=%lld N=%lld K=%lld: byte offsets beyond 31 bits", (long long)M,
                 (long long)N, (long long)K);
