@@ -105,6 +105,31 @@ __device__ __forceinline__ v4u sign_mask(const uint2 s) {
   return v4u{((s.x << 8) & 0x8000u) | ((s.x << 16) & 0x80000000u), ((s.x >> 8) & 0x8000u) | (s.x & 0x80000000u),
              ((s.y << 8) & 0x8000u) | ((s.y << 16) & 0x80000000u), ((s.y >> 8) & 0x8000u) | (s.y & 0x80000000u)};
 }
+// Code width of a kernel: 4 or 8 (asymmetric activation codes), or kSym4: the symmetric
+// 4-bit codes of weight rows (sq_pack_w4), quantized from the scaled values in the generic
+// kernel's steps, v = y / sqrt(K), t = v (1 / alpha), code = clamp(rint(t), -7, 7).
+constexpr int kSym4 = -4;
+constexpr int code_bits(int bits) { return bits == kSym4 ? 4 : bits; }
+
+// code + 8 (1 .. 15, exact) of one unscaled value; a NaN takes the lowest code
+__device__ __forceinline__ float sym_code8(float y, float s_n, float inv) {
+  const float t = __fmul_rn(__fmul_rn(y, s_n), inv);
+  return __fadd_rn(__builtin_rintf(__builtin_amdgcn_fmed3f(t, -7.0f, 7.0f)), 8.0f);
+}
+// Eight values' codes as one word of two's-complement nibbles; adds the sum of (code + 8) to sum8
+template <typename V>
+__device__ __forceinline__ uint32_t sym_word(const V& acc, int j0, float s_n, float inv, uint32_t& sum8) {
+  uint32_t ev = 0, od = 0;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    ev = __builtin_amdgcn_cvt_pk_u8_f32(sym_code8(acc[j0 + 2 * s], s_n, inv), s, ev);
+    od = __builtin_amdgcn_cvt_pk_u8_f32(sym_code8(acc[j0 + 2 * s + 1], s_n, inv), s, od);
+  }
+  sum8 = __builtin_amdgcn_sad_u8(ev, 0u, sum8);
+  sum8 = __builtin_amdgcn_sad_u8(od, 0u, sum8);
+  return (ev | (od << 4)) ^ 0x88888888u;  // c + 8 -> c
+}
+
 // and the code argument t clamped to [0, L], which a clipped range needs (v_cvt_pk_u8_f32
 // alone saturates at 255 only)
 template <bool VAR, int BITS>
@@ -460,8 +485,9 @@ struct Pair {
   static constexpr int SLOT = APAD * 128;                // bytes of one staged row
   static constexpr int ZERO_CHUNKS = (APAD - A) * 8;     // zero padding lines of a slot
   static constexpr int RED = 2 * ROWS * 2 * 2;           // floats: [parity][row][wave][min,max]
-  static constexpr int FLAGS = 2 * ROWS * 2;             // ints: [kind][row][wave] progress counters
-  static constexpr int LDS = HFRAG * 16 + ROWS * SLOT + RED * 4 + FLAGS * 4;
+  static constexpr int FLAGS = 3 * ROWS * 2;             // ints: [kind][row][wave] progress counters
+  static constexpr int SUMS = 2 * ROWS * 2;              // ints: [parity][row][wave] code sums (kSym4)
+  static constexpr int LDS = HFRAG * 16 + ROWS * SLOT + RED * 4 + FLAGS * 4 + SUMS * 4;
   static_assert(NT % 2 == 0 && NT * 32 >= A, "N tiles");
   static_assert(APAD % 16 == 0 && APAD >= A && A % 4 == 0, "padding");
   static_assert(ZERO_CHUNKS <= 128, "one zero chunk per thread of a wave pair");
@@ -489,6 +515,8 @@ had_quant_pair(RotQuantArgs args) {
   unsigned char* slots = smem + C::HFRAG * 16;
   float* red = reinterpret_cast<float*>(smem + C::HFRAG * 16 + C::ROWS * C::SLOT);
   int* flags = reinterpret_cast<int*>(smem + C::HFRAG * 16 + C::ROWS * C::SLOT + C::RED * 4);
+  int* sums = flags + C::FLAGS;
+  constexpr bool SYM = BITS == kSym4;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int p = wave >> 1;  // row slot
@@ -594,6 +622,7 @@ had_quant_pair(RotQuantArgs args) {
     reinterpret_cast<v4u*>(slot)[A * 8 + pl] = v4u{0u, 0u, 0u, 0u};
   // flags[k*2*ROWS + p*2 + h]: k = 0: min/max of iteration it published (it + 1);
   //                            k = 1: rows of iteration it stored to the slot (it + 1)
+  //                            k = 2: code sums of iteration it published (it + 1)
   int* const mine0 = flags + p * 2 + h;
   int* const mine1 = flags + 2 * C::ROWS + p * 2 + h;
   const int* const other0 = flags + p * 2 + (h ^ 1);
@@ -722,13 +751,17 @@ had_quant_pair(RotQuantArgs args) {
     float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
     for (int nt = 0; nt < C::NTW; ++nt) {
-      float tmn = acc[0][nt][0], tmx = acc[0][nt][0];
+      float tmn = SYM ? 0.0f : acc[0][nt][0], tmx = SYM ? 0.0f : acc[0][nt][0];
 #pragma unroll
       for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          tmn = fminf(tmn, acc[mt][nt][r]);
-          tmx = fmaxf(tmx, acc[mt][nt][r]);
+          if constexpr (SYM) {
+            tmx = fmaxf(tmx, fabsf(acc[mt][nt][r]));
+          } else {
+            tmn = fminf(tmn, acc[mt][nt][r]);
+            tmx = fmaxf(tmx, acc[mt][nt][r]);
+          }
         }
       if ((h * C::NTW + nt) * 32 + 32 <= A || (h * C::NTW + nt) * 32 + c < A) {
         mn = fminf(mn, tmn);
@@ -751,55 +784,89 @@ had_quant_pair(RotQuantArgs args) {
       store_row();
       if (lane == 0) pair_publish(mine1, it + 2);
     }
-    if constexpr (VAR) {  // clipped range [r min, r max]
-      mn = __fmul_rn(mn, args.clip);
-      mx = __fmul_rn(mx, args.clip);
-    }
-
-    // eq. 1 in the unscaled domain; reported alpha, beta carry the 1/sqrt(K) scale
-    const float r_u = __fsub_rn(mx, mn);
-    const float a_u = __fdiv_rn(r_u, BITS == 8 ? 255.0f : 15.0f);
-    const bool cst = __fmul_rn(a_u, s_n) < kMinNormal;
-    const float inv_u = cst ? 0.0f : __fdiv_rn(1.0f, a_u);
-    const float nb = -__fmul_rn(mn, inv_u);
-    if (valid && h == 0 && lane == 0) {
-      args.alpha[row] = cst ? 1.0f : __fmul_rn(a_u, s_n);
-      args.beta[row] = __fmul_rn(mn, s_n);
-    }
-
-    // ---- codes: lane (c, g) holds i_b = mt*32 + 16g + j (j = 0..15) of column j_a: bytes
-    // via v_cvt_pk_u8_f32 (even j in ev, odd j in od), ev | od << 4 is then four
-    // nibble-packed bytes; 8-byte store at output position j_a*64 + mt*32 + 16g.
-    uint8_t* qrow = args.q + row * (C::K * BITS / 8);
+    if constexpr (SYM) {
+      const float alpha = sym_alpha(__fmul_rn(mx, s_n));
+      const float inv = __fdiv_rn(1.0f, alpha);
+      uint8_t* qrow = args.q + row * (C::K / 2);
+      uint32_t sum8 = 0;
+      int count = 0;
 #pragma unroll
-    for (int nt = 0; nt < C::NTW; ++nt) {
-      const int ja = (h * C::NTW + nt) * 32 + c;
+      for (int nt = 0; nt < C::NTW; ++nt) {
+        const int ja = (h * C::NTW + nt) * 32 + c;
+        uint32_t ts8 = 0;
 #pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt) {
-        const int pos = ja * B + mt * 32 + 16 * g;
-        if constexpr (BITS == 8) {  // one code per byte: 16-byte store
-          uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-          for (int j = 0; j < 16; ++j) w[j >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][j], inv_u, nb)), j & 3, w[j >> 2]);
-          if (valid && ja < A) *reinterpret_cast<uint4*>(qrow + pos) = make_uint4(w[0], w[1], w[2], w[3]);
-        } else {
-          uint32_t w[2];
-#pragma unroll
-          for (int hw = 0; hw < 2; ++hw) {
-            uint32_t ev = 0, od = 0;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              ev = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][8 * hw + 2 * s], inv_u, nb)), s, ev);
-              od = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][8 * hw + 2 * s + 1], inv_u, nb)), s, od);
-            }
-            w[hw] = ev | (od << 4);
-          }
-          if (valid && ja < A) *reinterpret_cast<uint2*>(qrow + pos / 2) = make_uint2(w[0], w[1]);
+        for (int mt = 0; mt < C::MT; ++mt) {
+          const uint32_t w0 = sym_word(acc[mt][nt], 0, s_n, inv, ts8), w1 = sym_word(acc[mt][nt], 8, s_n, inv, ts8);
+          if (valid && ja < A) *reinterpret_cast<uint2*>(qrow + (ja * B + mt * 32 + 16 * g) / 2) = make_uint2(w0, w1);
         }
-        if constexpr (DBG) {
-          if (valid && ja < A) {
+        sum8 += ja < A ? ts8 : 0u;
+        count += ja < A ? 16 * C::MT : 0;
+      }
+      // the two waves' code sums meet in LDS (parity buffers, as for the min/max)
+      const int sum = wave_sum(static_cast<int>(sum8) - 8 * count);
+      int* const sm = sums + (it & 1) * (C::ROWS * 2) + p * 2;
+      if (lane == 0) {
+        sm[h] = sum;
+        pair_publish(flags + 4 * C::ROWS + p * 2 + h, it + 1);
+      }
+      if (h == 0) {
+        pair_wait(flags + 4 * C::ROWS + p * 2 + 1, it + 1);
+        if (valid && lane == 0) {
+          args.alpha[row] = alpha;
+          args.rowsum[row] = sum + sm[1];
+        }
+      }
+    } else {
+      if constexpr (VAR) {  // clipped range [r min, r max]
+        mn = __fmul_rn(mn, args.clip);
+        mx = __fmul_rn(mx, args.clip);
+      }
+
+      // eq. 1 in the unscaled domain; reported alpha, beta carry the 1/sqrt(K) scale
+      const float r_u = __fsub_rn(mx, mn);
+      const float a_u = __fdiv_rn(r_u, BITS == 8 ? 255.0f : 15.0f);
+      const bool cst = __fmul_rn(a_u, s_n) < kMinNormal;
+      const float inv_u = cst ? 0.0f : __fdiv_rn(1.0f, a_u);
+      const float nb = -__fmul_rn(mn, inv_u);
+      if (valid && h == 0 && lane == 0) {
+        args.alpha[row] = cst ? 1.0f : __fmul_rn(a_u, s_n);
+        args.beta[row] = __fmul_rn(mn, s_n);
+      }
+
+      // ---- codes: lane (c, g) holds i_b = mt*32 + 16g + j (j = 0..15) of column j_a: bytes
+      // via v_cvt_pk_u8_f32 (even j in ev, odd j in od), ev | od << 4 is then four
+      // nibble-packed bytes; 8-byte store at output position j_a*64 + mt*32 + 16g.
+      uint8_t* qrow = args.q + row * (C::K * BITS / 8);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) args.dbg[row * C::K + pos + j] = __fmul_rn(acc[mt][nt][j], s_n);
+      for (int nt = 0; nt < C::NTW; ++nt) {
+        const int ja = (h * C::NTW + nt) * 32 + c;
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt) {
+          const int pos = ja * B + mt * 32 + 16 * g;
+          if constexpr (BITS == 8) {  // one code per byte: 16-byte store
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) w[j >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][j], inv_u, nb)), j & 3, w[j >> 2]);
+            if (valid && ja < A) *reinterpret_cast<uint4*>(qrow + pos) = make_uint4(w[0], w[1], w[2], w[3]);
+          } else {
+            uint32_t w[2];
+#pragma unroll
+            for (int hw = 0; hw < 2; ++hw) {
+              uint32_t ev = 0, od = 0;
+#pragma unroll
+              for (int s = 0; s < 4; ++s) {
+                ev = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][8 * hw + 2 * s], inv_u, nb)), s, ev);
+                od = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][nt][8 * hw + 2 * s + 1], inv_u, nb)), s, od);
+              }
+              w[hw] = ev | (od << 4);
+            }
+            if (valid && ja < A) *reinterpret_cast<uint2*>(qrow + pos / 2) = make_uint2(w[0], w[1]);
+          }
+          if constexpr (DBG) {
+            if (valid && ja < A) {
+#pragma unroll
+              for (int j = 0; j < 16; ++j) args.dbg[row * C::K + pos + j] = __fmul_rn(acc[mt][nt][j], s_n);
+            }
           }
         }
       }
@@ -841,7 +908,7 @@ struct Lines {
   static constexpr int HCH = (A * A + 15) / 16;       // 16-byte chunks of H_A
   static constexpr int HPT = (HCH + THREADS - 1) / THREADS;
   static constexpr int STAGE = SLOT > HCH * 16 ? SLOT : HCH * 16;  // row slot, or H at the start
-  static constexpr int LDS = STAGE + 2 * NT * 4;      // + per-wave min/max
+  static constexpr int LDS = STAGE + 3 * NT * 4;      // + per-wave min/max, code sums (kSym4)
   static_assert(F == 8 || F == 16, "a fragment in one H_A entry, one S_F pattern for all k-steps");
   static_assert(NT * 32 >= AD && (NT - 1) * 32 < AD, "one N tile per wave, none empty");
   static_assert(ZERO_CHUNKS <= THREADS, "padding lines zeroed in one pass");
@@ -855,6 +922,8 @@ had_quant_lines(RotQuantArgs args) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* slot = smem;
   float* red = reinterpret_cast<float*>(smem + C::STAGE);
+  int* sums = reinterpret_cast<int*>(red + 2 * NT);
+  constexpr bool SYM = BITS == kSym4;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int g = lane >> 5;
@@ -1049,17 +1118,21 @@ had_quant_lines(RotQuantArgs args) {
     }
 
     // ---- row min/max over real lines (padding lines hold zeros)
-    float mn = acc[0][0], mx = acc[0][0];
+    float mn = SYM ? 0.0f : acc[0][0], mx = SYM ? 0.0f : acc[0][0];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        mn = fminf(mn, acc[mt][r]);
-        mx = fmaxf(mx, acc[mt][r]);
+        if constexpr (SYM) {
+          mx = fmaxf(mx, fabsf(acc[mt][r]));
+        } else {
+          mn = fminf(mn, acc[mt][r]);
+          mx = fmaxf(mx, acc[mt][r]);
+        }
       }
     if (!real) {
-      mn = INFINITY;
-      mx = -INFINITY;
+      mn = SYM ? 0.0f : INFINITY;
+      mx = SYM ? 0.0f : -INFINITY;
     }
     mn = wave_min(mn);
     mx = wave_max(mx);
@@ -1076,54 +1149,78 @@ had_quant_lines(RotQuantArgs args) {
       mx = fmaxf(mx, red[NT + v]);
     }
     if (more) store_row();
-    if constexpr (VAR) {  // clipped range [r min, r max]
-      mn = __fmul_rn(mn, args.clip);
-      mx = __fmul_rn(mx, args.clip);
-    }
-
-    // eq. 1 in the unscaled domain; reported alpha, beta carry the 1/sqrt(K) scale
-    const float r_u = __fsub_rn(mx, mn);
-    const float a_u = __fdiv_rn(r_u, BITS == 8 ? 255.0f : 15.0f);
-    const bool cst = __fmul_rn(a_u, s_n) < kMinNormal;
-    const float inv_u = cst ? 0.0f : __fdiv_rn(1.0f, a_u);
-    const float nb = -__fmul_rn(mn, inv_u);
-    if (threadIdx.x == 0) {
-      args.alpha[row] = cst ? 1.0f : __fmul_rn(a_u, s_n);
-      args.beta[row] = __fmul_rn(mn, s_n);
-    }
-
-    // ---- codes of line n, columns 32 mt + 16 g .. + 15: 8-byte stores
-    uint8_t* qrow = args.q + row * (C::K * BITS / 8);
+    float alpha_w = 0.0f;
+    if constexpr (SYM) {
+      alpha_w = sym_alpha(__fmul_rn(mx, s_n));
+      const float inv = __fdiv_rn(1.0f, alpha_w);
+      uint8_t* qrow = args.q + row * (C::K / 2);
+      uint32_t sum8 = 0;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const int pos = n * 64 + mt * 32 + 16 * g;
-      if constexpr (BITS == 8) {  // one code per byte: 16-byte store
-        uint32_t wd[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 16; ++j) wd[j >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][j], inv_u, nb)), j & 3, wd[j >> 2]);
-        if (real) *reinterpret_cast<uint4*>(qrow + pos) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-      } else {
-        uint32_t wd[2];
-#pragma unroll
-        for (int hw = 0; hw < 2; ++hw) {
-          uint32_t ev = 0, od = 0;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            ev = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][8 * hw + 2 * s], inv_u, nb)), s, ev);
-            od = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][8 * hw + 2 * s + 1], inv_u, nb)), s, od);
-          }
-          wd[hw] = ev | (od << 4);
-        }
-        if (real) *reinterpret_cast<uint2*>(qrow + pos / 2) = make_uint2(wd[0], wd[1]);
+      for (int mt = 0; mt < 2; ++mt) {
+        const uint32_t w0 = sym_word(acc[mt], 0, s_n, inv, sum8), w1 = sym_word(acc[mt], 8, s_n, inv, sum8);
+        if (real) *reinterpret_cast<uint2*>(qrow + (n * 64 + mt * 32 + 16 * g) / 2) = make_uint2(w0, w1);
       }
-      if constexpr (DBG) {
-        if (real) {
+      const int sum = wave_sum(real ? static_cast<int>(sum8) - 8 * 32 : 0);
+      if (lane == 0) sums[w] = sum;
+    } else {
+      if constexpr (VAR) {  // clipped range [r min, r max]
+        mn = __fmul_rn(mn, args.clip);
+        mx = __fmul_rn(mx, args.clip);
+      }
+
+      // eq. 1 in the unscaled domain; reported alpha, beta carry the 1/sqrt(K) scale
+      const float r_u = __fsub_rn(mx, mn);
+      const float a_u = __fdiv_rn(r_u, BITS == 8 ? 255.0f : 15.0f);
+      const bool cst = __fmul_rn(a_u, s_n) < kMinNormal;
+      const float inv_u = cst ? 0.0f : __fdiv_rn(1.0f, a_u);
+      const float nb = -__fmul_rn(mn, inv_u);
+      if (threadIdx.x == 0) {
+        args.alpha[row] = cst ? 1.0f : __fmul_rn(a_u, s_n);
+        args.beta[row] = __fmul_rn(mn, s_n);
+      }
+
+      // ---- codes of line n, columns 32 mt + 16 g .. + 15: 8-byte stores
+      uint8_t* qrow = args.q + row * (C::K * BITS / 8);
 #pragma unroll
-          for (int j = 0; j < 16; ++j) args.dbg[row * C::K + pos + j] = __fmul_rn(acc[mt][j], s_n);
+      for (int mt = 0; mt < 2; ++mt) {
+        const int pos = n * 64 + mt * 32 + 16 * g;
+        if constexpr (BITS == 8) {  // one code per byte: 16-byte store
+          uint32_t wd[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int j = 0; j < 16; ++j) wd[j >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][j], inv_u, nb)), j & 3, wd[j >> 2]);
+          if (real) *reinterpret_cast<uint4*>(qrow + pos) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+        } else {
+          uint32_t wd[2];
+#pragma unroll
+          for (int hw = 0; hw < 2; ++hw) {
+            uint32_t ev = 0, od = 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              ev = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][8 * hw + 2 * s], inv_u, nb)), s, ev);
+              od = __builtin_amdgcn_cvt_pk_u8_f32(code_arg<VAR, BITS>(__fmaf_rn(acc[mt][8 * hw + 2 * s + 1], inv_u, nb)), s, od);
+            }
+            wd[hw] = ev | (od << 4);
+          }
+          if (real) *reinterpret_cast<uint2*>(qrow + pos / 2) = make_uint2(wd[0], wd[1]);
+        }
+        if constexpr (DBG) {
+          if (real) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) args.dbg[row * C::K + pos + j] = __fmul_rn(acc[mt][j], s_n);
+          }
         }
       }
     }
     __syncthreads();  // the slot holds the next row; the min/max slots are free again
+    if constexpr (SYM) {  // the sums' slots are written again behind the next min/max barrier
+      if (threadIdx.x == 0) {
+        int sum = 0;
+#pragma unroll
+        for (int v = 0; v < NT; ++v) sum += sums[v];
+        args.alpha[row] = alpha_w;
+        args.rowsum[row] = sum;
+      }
+    }
     if (!more) break;
     row = next;
   }
@@ -1210,7 +1307,32 @@ hipError_t launch_lines(const RotQuantArgs& a, hipStream_t stream) {
   });
 }
 
+// The pair and line kernels stage rows in 16-byte chunks and read S 8 entries at a time.
+bool staged_ok(const RotQuantArgs& a) {
+  return (reinterpret_cast<uintptr_t>(a.x) & 15) == 0 && (a.ldx % 8) == 0 &&
+         (reinterpret_cast<uintptr_t>(a.H) & 15) == 0 && (reinterpret_cast<uintptr_t>(a.signs) & 7) == 0;
+}
+
 }  // namespace
+
+// Weight rows through the same kernels with symmetric codes: bound, like the activation rows,
+// by vector issue and not by memory.  Measured on MI355X (us, against the generic kernel,
+// whose scalar dense stage reads a factor entry and an element per product):
+//   [4096 x 11008] H_172 (x) S_64 38.8 vs 7707   [4096 x 14336] H_28 (x) S_512 49.4 vs 2193
+//   [8192 x 28672] H_28 (x) S_1024 290 vs 16230
+hipError_t launch_pack_kron(const RotQuantArgs& a, hipStream_t stream) {
+  if (a.K != static_cast<int64_t>(a.a) * a.b || a.H == nullptr || !staged_ok(a)) return hipErrorNotSupported;
+  if (a.a == 28 && a.b == 512)
+    return a.signs ? launch_lines_t<28, 8, 7, false, kSym4, true>(a, stream)
+                   : launch_lines_t<28, 8, 7, false, kSym4, false>(a, stream);
+  if (a.a == 172 && a.b == 64)
+    return a.signs ? launch_pair_t<172, 176, 6, false, kSym4, true>(a, stream)
+                   : launch_pair_t<172, 176, 6, false, kSym4, false>(a, stream);
+  if (a.a == 28 && a.b == 1024)
+    return a.signs ? launch_lines_t<28, 16, 14, false, kSym4, true>(a, stream)
+                   : launch_lines_t<28, 16, 14, false, kSym4, false>(a, stream);
+  return hipErrorNotSupported;
+}
 
 // Returns hipErrorNotSupported when no fast path covers the arguments.
 hipError_t launch_had_quant_kron(const RotQuantArgs& a, hipStream_t stream) {
@@ -1219,9 +1341,7 @@ hipError_t launch_had_quant_kron(const RotQuantArgs& a, hipStream_t stream) {
   // the pair and line kernels stage rows in 16-byte chunks (and write 4- or 8-bit codes,
   // with or without the clipping and sign variants; S is read 8 entries at a time); the
   // register-prefetch kernels write plain 4-bit codes only
-  const bool pair_ok = (reinterpret_cast<uintptr_t>(a.x) & 15) == 0 && (a.ldx % 8) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.H) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.signs) & 7) == 0;
+  const bool pair_ok = staged_ok(a);
   if (!pair_ok && (a.bits != 4 || is_variant(a))) return hipErrorNotSupported;
   if (a.a == 28 && a.b == 512) {
     if (pair_ok) return launch_lines<28, 8, 7>(a, stream);

@@ -39,6 +39,8 @@ hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream);
 // Fast path for K = a*b rows with a registered dense order, per-token 4-bit groups;
 // hipErrorNotSupported when it does not apply.
 hipError_t launch_had_quant_kron(const RotQuantArgs& a, hipStream_t stream);
+// The same for weight rows (symmetric codes, row sums); hipErrorNotSupported likewise.
+hipError_t launch_pack_kron(const RotQuantArgs& a, hipStream_t stream);
 // Rotation + symmetric per-row 4-bit quantization of weight rows, with code row sums.
 hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream);
 
