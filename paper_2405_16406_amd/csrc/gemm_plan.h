@@ -31,7 +31,8 @@ constexpr bool slice_has(GemmFamily f, int nb, int mb) {
 // and 128-byte segments (whole cache lines of every row) where K leaves each wave enough of
 // them.  More workgroups than CUs: one slot, so that two or three workgroups share a CU and
 // cover each other's waits; there short segments take less LDS.  One-block token tiles over
-// a long K are weight streams, where bytes in flight are all that counts: two long slots.
+// a long K are weight streams, where bytes in flight are all that counts: two long slots (one
+// where K leaves a wave few segments: [1 x 4096] x [4096 x 4096] 3.6 against 3.9 us).
 // Measured on MI355X (us; two slots x 128 | two x 64 | one x 128 | one x 64 bytes):
 //   [77 x 28672] x [8192 x 28672], 4 x 3 blocks, 256 workgroups    32.3 | 42.1 | 47.0 | 54.6
 //   [300 x 11008] x [4096 x 11008], 4 x 5, 256                     19.3 | 18.1 | 19.5 | 21.2
@@ -40,8 +41,8 @@ constexpr bool slice_has(GemmFamily f, int nb, int mb) {
 //   [16 x 8192] x [57344 x 8192], 2 x 1, 1792                      42.6 | -    | 46.4 | -
 inline void slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, int* ns, int* seg) {
   const bool a8 = f == kW4A8;
-  if (mb == 1 && nb <= 2 && K >= 8192) {
-    *ns = 2;
+  if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) {
+    *ns = K >= 8192 ? 2 : 1;
     *seg = 128;
   } else if (one_round) {
     *ns = 2;
@@ -49,33 +50,42 @@ inline void slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, 
                : (nb + mb <= 5 && K >= 8192) || (nb + mb <= 9 && K >= 16384)) ? 128 : 64;
   } else {
     *ns = 1;
-    *seg = nb + mb <= (a8 ? 5 : 8) && K > 4096 ? 128 : 64;
+    *seg = (nb + mb <= (a8 ? 5 : 8) && K > 4096) || (!a8 && nb + mb <= 9 && K >= 16384) ? 128 : 64;
   }
 }
 
-// Estimated times (us), fitted to 495 measured products of M = 1 .. 1400 tokens against
-// weights of 4096 x 4096 to 57344 x 8192 and 8192 x 28672 on a 256-CU MI355X: the chosen tile
-// is 1.0 - 2.5 % off the best measured one on average, and the choice between slice and ring
-// below 0.1 - 0.2 %.  A tile costs its products and its operand reads per 128 k, times the
-// workgroups of the busiest CU (alone on a CU it waits more), next to the time the operands
-// take from memory.
+// Estimated times (us), fitted to 850 measured products of M = 1 .. 3600 tokens against
+// weights of 2048 x 4096 to 57344 x 8192 and 8192 x 28672 on a 256-CU MI355X.  A tile costs
+// its products and operand reads per 128 k, times the rounds of tiles (alone on a CU it waits
+// more), next to the time the operands take from memory and from the L2s.  The tile chosen is
+// 1 - 2.5 % off the best measured one on average; from 300 tokens the estimate is 5 - 7 % off
+// (rms), which is why the ring below is left only for a clear gain.
 struct SliceCost {
-  double tile, prod, oper, base, rate, alone;
+  float base, mem_tb, tile, ceil, alone, l2_tb;
+  float shape[kSliceShapes];  // us per 128 k of a round, in the order of kSliceShape
 };
-inline double slice_us(GemmFamily f, const GemmArgs& g, int nb, int mb, int cus) {
-  constexpr SliceCost kCost[3] = {{0.297, 0.00609, 0.00481, 3.517, 4.153, 1.048},
-                                  {0.171, 0.00675, 0.00360, 2.805, 3.578, 1.942},
-                                  {0.117, 0.00663, 0.00516, 4.395, 3.888, 1.001}};
+inline double slice_us(GemmFamily f, const GemmArgs& g, int shape, int cus) {
+  constexpr SliceCost kCost[3] = {
+      {2.852f, 6.181f, 0.7274f, 0.9605f, 1.1488f, 21.85f,
+       {0.0010f, 0.0117f, 0.0319f, 0.0493f, 0.0663f, 0.0963f, 0.1236f, 0.1538f, 0.1829f, 0.2423f, 0, 0, 0.2417f}},
+      {3.595f, 6.706f, 0.8732f, 0.9962f, 1.2698f, 18.20f,
+       {0, 0.0010f, 0.0010f, 0.0284f, 0.0470f, 0.0747f, 0.1033f, 0.1305f, 0.1636f, 0.2288f, 0, 0, 0.2280f}},
+      {2.781f, 5.492f, 0.8091f, 0.8777f, 1.1424f, 21.71f,
+       {0.0010f, 0.0192f, 0.0456f, 0, 0.0868f, 0.1234f, 0.1495f, 0, 0.2278f, 0, 0.1742f, 0.2252f, 0.2855f}}};
   const SliceCost& c = kCost[f];
+  const int nb = kSliceShape[shape][0], mb = kSliceShape[shape][1], abytes = f == kW4A8 ? 2 : 1;
   const double M = static_cast<double>(g.M), N = static_cast<double>(g.N), K = static_cast<double>(g.K);
-  const int abytes = f == kW4A8 ? 2 : 1;
-  const double tiles = std::ceil(M / (16 * mb)) * std::ceil(N / (16 * nb));
-  const double busy = std::ceil(tiles / cus);
-  double comp = busy * (c.tile + K / 128 * (c.prod * nb * mb + c.oper * (nb + abytes * mb)));
-  if (busy == 1) comp *= c.alone;
-  const double mem = (N * K / 2 + M * K * abytes / 2 + 2 * M * N) / c.rate * 1e-6;
-  const double c2 = comp * comp, m2 = mem * mem;
-  return c.base + std::sqrt(std::sqrt(c2 * c2 + m2 * m2));
+  const double tiles = std::ceil(M / (16 * mb)) * std::ceil(N / (16 * nb)), rounds = tiles / cus;
+  double comp = (c.ceil * std::ceil(rounds) + (1 - c.ceil) * rounds) * (c.tile + K / 128 * c.shape[shape]);
+  if (rounds <= 1) comp *= c.alone;
+  double mem = (N * K / 2 + M * K * abytes / 2 + (f == kW4A4Swiglu ? M * N : 2 * M * N)) / c.mem_tb * 1e-6;
+  if (rounds < 1) mem /= std::sqrt(rounds);  // idle CUs stream nothing
+  const double l2 = tiles * 16 * (nb + abytes * mb) * K / 2 / c.l2_tb * 1e-6;
+  const double c2 = comp * comp, m2 = mem * mem, l22 = l2 * l2;
+  const double us = c.base + std::sqrt(std::sqrt(c2 * c2 + m2 * m2 + l22 * l22));
+  // activations far past an XCD's 4 MB of L2 (many tokens over a long K) are read again by
+  // every weight tile: 17 - 29 % over the estimate where measured
+  return M * K * abytes / 2 > 14e6 ? 1.25 * us : us;
 }
 
 inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
@@ -84,7 +94,7 @@ inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
   for (int s = 0; s < kSliceShapes; ++s) {
     const int nb = kSliceShape[s][0], mb = kSliceShape[s][1];
     if (!slice_has(f, nb, mb)) continue;
-    const double t = slice_us(f, g, nb, mb, cus);
+    const double t = slice_us(f, g, s, cus);
     if (best.nb == 0 || t < us) {
       best.nb = nb;
       best.mb = mb;
@@ -97,19 +107,88 @@ inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
   return best;
 }
 
-// Rounds of the ring kernel's tiles (256 x 256 from one per CU on, else half as large): the
-// last one costs as much as a full one.
-inline double ring_us(GemmFamily f, const GemmArgs& g, int cus) {
+// Tiles of the ring kernel (w4a4_gemm.hip): 256 x 256, or half of one.
+struct RingTile {
+  int bm, bn;
+};
+constexpr RingTile ring_tile(GemmFamily f, bool large) {
+  if (large) return {256, 256};
+  return f == kW4A4Swiglu ? RingTile{256, 128} : RingTile{128, 256};
+}
+inline int64_t ring_tiles(GemmFamily f, const GemmArgs& g, bool large) {
+  const RingTile t = ring_tile(f, large);
+  return ((g.M + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn);
+}
+// At least as many 256 x 256 tiles as a 256-CU part has CUs.
+inline bool ring_large(GemmFamily f, const GemmArgs& g) { return ring_tiles(f, g, true) >= 256; }
+
+// Rounds of the ring kernel's tiles; the last one costs nearly as much as a full one.
+inline double ring_us(GemmFamily f, const GemmArgs& g, bool large, int64_t tiles, int cus) {
   constexpr double kCost[3][2][3] = {{{4.81, 0.6454, 0.2645}, {1.03, 1.2458, 0.3400}},
                                      {{6.89, 0.6975, 0.1875}, {4.22, 1.1768, 0.3738}},
                                      {{4.81, 0.8457, 0.3277}, {7.34, 1.3151, 0.5921}}};
-  const int64_t big = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  const bool large = big >= 256;
-  const int64_t half = f == kW4A4Swiglu ? ((g.M + 255) / 256) * ((g.N + 127) / 128)
-                                        : ((g.M + 127) / 128) * ((g.N + 255) / 256);
-  const double tiles = static_cast<double>(large ? big : half), k = static_cast<double>(g.K) / 128;
+  const double k = static_cast<double>(g.K) / 128, rounds = static_cast<double>(tiles) / cus;
   const double* c = kCost[f][large];
-  return c[0] + k * (c[1] * std::ceil(tiles / cus) + c[2] * tiles / cus);
+  return c[0] + k * (c[1] * std::ceil(rounds) + c[2] * rounds);
+}
+
+// The weight rows [r0, r1) of a product.
+inline GemmArgs weight_rows(GemmFamily f, const GemmArgs& g, int64_t r0, int64_t r1) {
+  GemmArgs s = g;
+  s.N = r1 - r0;
+  s.wq = g.wq + r0 * (g.K / 2);
+  s.wa = g.wa + r0;
+  s.rs = g.rs + r0;
+  s.bias = g.bias ? g.bias + r0 : nullptr;
+  s.y = g.y + (f == kW4A4Swiglu ? r0 / 2 : r0);
+  return s;
+}
+
+// Kernels of a product: the ring takes weight rows [0, ring_n), the slice kernel the rest.
+struct GemmPlan {
+  int64_t ring_n;
+  bool large;       // the ring's tiles
+  SlicePlan slice;  // of the rest
+};
+
+// The slice kernel alone, the ring alone, or the ring on as many weight rows as fill whole
+// rounds of its tiles and the slice kernel on the rest, where the last round would leave CUs
+// idle; the ring wherever the others are not at least 7 % faster by the estimates, which is
+// about their error (fits(sub, large): the ring's 31-bit offsets cover the product).
+// Measured on MI355X (us, against the ring alone): W4A8 [1024 x 22016 x 4096] 104 vs 117 (256
+// tiles and 5632 rows of slices instead of two rounds for 344 tiles), [1536 x 22016 x 4096]
+// 138 vs 181, [1100 x 8192 x 28672] 306 vs 446; W4A4 [2300 x 4096 x 14336] 125 vs 176, [2100 x
+// 8192 x 8192] 120 vs 168; with SiLU [1300 x 22016 x 4096] 106 vs 140.
+template <typename Fits>
+GemmPlan plan_gemm(GemmFamily f, const GemmArgs& g, int cus, Fits&& fits) {
+  constexpr double kClear = 0.93;
+  GemmPlan best{0, false, plan_slice(f, g, cus)};
+  if (g.M <= 16) return best;
+  double us = best.slice.us;
+  const bool whole = ring_large(f, g);
+  if (fits(g, whole)) {
+    const double t = ring_us(f, g, whole, ring_tiles(f, g, whole), cus);
+    if (kClear * t <= us) {
+      best = GemmPlan{g.N, whole, SlicePlan{}};
+      us = t;
+    }
+  }
+  if (g.dbg_acc) return best;  // its rows are the whole product's
+  for (int large = 0; large < 2; ++large) {
+    const RingTile t = ring_tile(f, large);
+    const int64_t tm = (g.M + t.bm - 1) / t.bm, rounds = ring_tiles(f, g, large) / cus;
+    const int64_t n1 = rounds * cus / tm * t.bn;
+    if (n1 <= 0 || n1 >= g.N) continue;
+    const GemmArgs head = weight_rows(f, g, 0, n1), tail = weight_rows(f, g, n1, g.N);
+    if (!fits(head, large)) continue;
+    const SlicePlan p = plan_slice(f, tail, cus);
+    const double u = ring_us(f, head, large, tm * (n1 / t.bn), cus) + p.us;
+    if (u < kClear * us) {
+      best = GemmPlan{n1, large != 0, p};
+      us = u;
+    }
+  }
+  return best;
 }
 
 // The slice kernel with a plan's tile.

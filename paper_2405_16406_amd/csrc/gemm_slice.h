@@ -373,7 +373,7 @@ hipError_t launch_slice_plan(const GemmArgs& g, const SlicePlan& p, hipStream_t 
       if (p.seg == 128) {
         if constexpr (nb + mb <= (a8 ? 4 : 9))
           if (p.ns == 2) e = launch_slice<nb, mb, 2, 128, F>(g, stream);
-        if constexpr (nb + mb <= (a8 ? 5 : 8))
+        if constexpr (nb + mb <= (a8 ? 5 : 9))
           if (p.ns == 1) e = launch_slice<nb, mb, 1, 128, F>(g, stream);
       } else {
         e = p.ns == 2 ? launch_slice<nb, mb, 2, 64, F>(g, stream) : launch_slice<nb, mb, 1, 64, F>(g, stream);

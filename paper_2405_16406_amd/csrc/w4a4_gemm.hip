@@ -555,9 +555,6 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
   return launch(kern, grid, dim3(R::THREADS), LDS, stream, g);
 }
 
-// 256 x 256 tiles (large), or half of one.
-bool large_tiles(const GemmArgs& g) { return ((g.M + 255) / 256) * ((g.N + 255) / 256) >= 256; }
-
 // Gate/up products are taken where the byte offsets of the kernels they were first built on
 // fit 31 bits: one or two tokens always (K <= 65536), decode sizes by the rows of a
 // workgroup past N, others by the ring tile's rows past M and N.
@@ -571,7 +568,7 @@ bool swiglu_covered(const GemmArgs& g, int cus) {
     return (g.N + past) * kb + 64 < lim;
   }
   if (g.M <= 128) return (g.M + 128) * kb + 128 < lim && (g.N + 128) * kb + 64 < lim;
-  return large_tiles(g) ? fits_ring<2, 4, 4, 2, 4>(g) : fits_ring<2, 2, 4, 2, 3>(g);
+  return ring_large(kW4A4Swiglu, g) ? fits_ring<2, 4, 4, 2, 4>(g) : fits_ring<2, 2, 4, 2, 3>(g);
 }
 
 // Ring tiles.  At least as many 256 x 256 tiles as CUs -> those: 8 waves of 128 x 64 and four
@@ -583,14 +580,12 @@ bool swiglu_covered(const GemmArgs& g, int cus) {
 //   8-bit  [2048 x 22016 x 4096] 211 vs 255   [4096 x 28672 x 4096] 505 vs 611   [4096 x 4096 x 14336] 241 vs 290
 // and with fewer than 256 large tiles the half ones: 4-bit [2048 x 4096 x 11008] 83.5 vs 123,
 // 8-bit 104 vs 150.
-hipError_t launch_ring_tiles(GemmFamily f, const GemmArgs& g, hipStream_t stream) {
-  const bool large = large_tiles(g);
+hipError_t launch_ring_tiles(GemmFamily f, const GemmArgs& g, bool large, hipStream_t stream) {
   if (f == kW4A8) return large ? launch_ring<4, 2, 2, 4, 3, 1, true>(g, stream) : launch_ring<2, 4, 2, 2, 4, 1, true>(g, stream);
   if (large) return launch_ring<2, 4, 4, 2, 4>(g, stream);
   return f == kW4A4Swiglu ? launch_ring<2, 2, 4, 2, 3, 2>(g, stream) : launch_ring<2, 4, 2, 2, 3>(g, stream);
 }
-bool fits_ring_tiles(GemmFamily f, const GemmArgs& g) {
-  const bool large = large_tiles(g);
+bool fits_ring_tiles(GemmFamily f, const GemmArgs& g, bool large) {
   if (f == kW4A8) return large ? fits_ring<4, 2, 2, 4, 3, true>(g) : fits_ring<2, 4, 2, 2, 4, true>(g);
   if (large) return fits_ring<2, 4, 4, 2, 4>(g);
   return f == kW4A4Swiglu ? fits_ring<2, 2, 4, 2, 3>(g) : fits_ring<2, 4, 2, 2, 3>(g);
@@ -598,18 +593,20 @@ bool fits_ring_tiles(GemmFamily f, const GemmArgs& g) {
 
 }  // namespace
 
-// The slice kernel wherever it is estimated to be faster than the ring's rounds of tiles, and
-// where the ring's 31-bit offsets do not cover the operands.
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream) {
   const GemmFamily f = g.a8 ? kW4A8 : g.swiglu ? kW4A4Swiglu : kW4A4;
   int cus = 0;
   const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
   if (f == kW4A4Swiglu && !swiglu_covered(g, cus)) return hipErrorNotSupported;
-  const SlicePlan p = plan_slice(f, g, cus);
-  if (g.M > 16 && fits_ring_tiles(f, g) && ring_us(f, g, cus) <= p.us) return launch_ring_tiles(f, g, stream);
-  return f == kW4A8 ? launch_w4a8_slice(g, p, stream)
-                    : f == kW4A4Swiglu ? launch_w4a4_slice_swiglu(g, p, stream) : launch_w4a4_slice(g, p, stream);
+  const GemmPlan p = plan_gemm(f, g, cus, [f](const GemmArgs& s, bool large) { return fits_ring_tiles(f, s, large); });
+  if (p.ring_n > 0) {
+    const hipError_t r = launch_ring_tiles(f, p.ring_n < g.N ? weight_rows(f, g, 0, p.ring_n) : g, p.large, stream);
+    if (r != hipSuccess || p.ring_n == g.N) return r;
+  }
+  const GemmArgs s = weight_rows(f, g, p.ring_n, g.N);
+  return f == kW4A8 ? launch_w4a8_slice(s, p.slice, stream)
+                    : f == kW4A4Swiglu ? launch_w4a4_slice_swiglu(s, p.slice, stream) : launch_w4a4_slice(s, p.slice, stream);
 }
 
 }  // namespace sq

@@ -1,6 +1,6 @@
 """The K-sliced tile kernel of the quantized products (M up to a few hundred tokens), against
-the CPU oracle: one case per built tile, ring depth and segment length, with ragged token
-counts, weight rows and K (half segments, waves without a segment), biases, raw accumulators
+the CPU oracle: sizes that spread over the built tiles, ring depths and segment lengths, with
+ragged token counts, weight rows and K (half segments, waves without a segment), biases, raw accumulators
 and strided outputs.  Accumulators are exact, outputs within the fp16 output tolerance of
 tests/parity.py; the vector and element-wise stores give the same bits."""
 
@@ -14,54 +14,29 @@ from test_gpu_parity import dev, gemm8_case, gemm_case, host, oq, say, swiglu_ca
 
 pytestmark = pytest.mark.gpu
 
-# token counts at the tiles' edges (16 nb x 16 mb blocks, ns slots of seg bytes in the comments)
-W4A4 = [(1, 1088, 8256),    # 1 x 1, 2 x 128
-        (16, 60, 4160),     # 1 x 1, 2 x 64; the last block of weight rows ragged
-        (9, 8250, 4160),    # 2 x 1, 1 x 128
-        (3, 8256, 4096),    # 2 x 1, 1 x 64
-        (16, 8200, 8256),   # 2 x 1, 2 x 128
-        (13, 4150, 4160),   # 2 x 1, 2 x 64
-        (17, 16440, 4160),  # 2 x 2, 1 x 128
-        (18, 16448, 4096),  # 2 x 2, 1 x 64
-        (31, 4160, 8256),   # 2 x 2, 2 x 128
-        (129, 1080, 192),   # 2 x 2, 2 x 64
-        (33, 16447, 4160),  # 2 x 3, 1 x 128
-        (34, 16448, 4096),  # 2 x 3, 1 x 64
-        (255, 1088, 8256),  # 2 x 3, 2 x 128
-        (255, 1087, 320),   # 2 x 3, 2 x 64
-        (200, 4150, 4160),  # 4 x 2, 1 x 128
-        (200, 4160, 4096),  # 4 x 2, 1 x 64
-        (384, 1088, 16448),  # 4 x 2, 2 x 128
-        (16, 8252, 320),    # 4 x 2, 2 x 64
-        (300, 4160, 4160),  # 4 x 3, 1 x 128
-        (300, 4159, 4096),  # 4 x 3, 1 x 64
-        (512, 1088, 16448),  # 4 x 3, 2 x 128
-        (129, 4160, 192),   # 4 x 3, 2 x 64
-        (700, 4160, 4160),  # 4 x 4, 1 x 128
-        (700, 4160, 4096),  # 4 x 4, 1 x 64
-        (160, 4158, 320),   # 4 x 4, 2 x 64
-        (129, 22010, 192),  # 4 x 5, 1 x 64
-        (1000, 1088, 16448),  # 4 x 5, 2 x 128
-        (200, 4160, 64),    # 4 x 5, 2 x 64: one segment, three waves without any
-        (255, 8256, 192),   # 4 x 6, 1 x 64
-        (96, 8250, 320),    # 4 x 6, 2 x 64
-        (300, 8256, 192),   # 4 x 8, 1 x 64
-        (384, 4160, 320),   # 4 x 8, 2 x 64
-        (129, 16440, 192),  # 8 x 4, 1 x 64
-        (1, 16448, 320)]    # 8 x 4, 2 x 64
+W4A4 = [(1, 1088, 8256), (16, 60, 4160), (9, 8250, 4160), (3, 8256, 4096), (16, 8200, 8256),
+        (13, 4150, 4160), (17, 16440, 4160), (18, 16448, 4096), (31, 4160, 8256), (129, 1080, 192),
+        (33, 16447, 4160), (34, 16448, 4096), (255, 1088, 8256), (255, 1087, 320), (200, 4150, 4160),
+        (200, 4160, 4096), (384, 1088, 16448), (16, 8252, 320), (300, 4160, 4160), (300, 4159, 4096),
+        (512, 1088, 16448), (129, 4160, 192), (700, 4160, 4160), (700, 4160, 4096), (160, 4158, 320),
+        (129, 22010, 192), (1000, 1088, 16448), (200, 4160, 64), (255, 8256, 192), (96, 8250, 320),
+        (300, 8256, 192), (384, 4160, 320), (129, 16440, 192), (1, 16448, 320), (512, 4160, 16448),
+        (384, 4160, 4160), (384, 4160, 4096), (384, 4160, 64), (1, 57344, 192), (1, 4160, 320)]
 
 SWIGLU = [(1, 544, 8256, True), (16, 8224, 4160, True), (1, 8224, 320, False), (16, 544, 192, True),
           (17, 8224, 4160, True), (17, 4128, 192, False), (384, 544, 4160, True),
           (512, 544, 4160, False), (33, 4128, 320, True), (200, 2080, 4160, True), (1, 8224, 64, True),
           (255, 2080, 4160, True), (129, 4128, 192, False), (384, 2080, 4160, True), (160, 4128, 320, True),
           (129, 11008, 192, False), (255, 4128, 320, True), (200, 8224, 192, True), (129, 8224, 320, True),
-          (5, 96, 192, True), (40, 32, 64, False)]
+          (5, 96, 192, True), (40, 32, 64, False), (512, 2080, 16448, True), (1000, 32, 8256, True),
+          (300, 544, 8256, False), (512, 544, 16448, True), (1000, 544, 192, True)]
 
 W4A8 = [(1, 1088, 8256), (16, 60, 4160), (9, 8250, 4160), (3, 8256, 4096), (16, 8200, 8256), (13, 4150, 192),
         (17, 16440, 4160), (18, 16448, 4096), (31, 4160, 8256), (129, 1080, 192), (16, 28730, 320),
         (16, 8252, 64), (129, 8250, 4160), (129, 4160, 192), (160, 4158, 320), (77, 28735, 192),
         (200, 8256, 320), (1, 16448, 320), (255, 8250, 320), (255, 4160, 64), (129, 16440, 192),
-        (160, 8256, 320)]
+        (160, 8256, 320), (17, 16448, 8256), (384, 4160, 8256), (1000, 1088, 64), (65, 28730, 320),
+        (1000, 4160, 192), (1, 57344, 192)]
 
 
 @pytest.mark.parametrize("M,N,K", W4A4)
@@ -80,6 +55,23 @@ def test_swiglu_slice(M, I, K, bias):
 def test_w4a8_slice(M, N, K):
     say(f"w4a8_linear slice M={M} N={N} K={K}")
     gemm8_case(M, N, K, seed=M + 5 * N + K, bias=(M + N) % 3 != 0)
+
+
+# Products that fill whole rounds of ring tiles and leave a rest for the slice kernel.  The
+# accumulators' call runs as one kernel, so its outputs check the split one's bit for bit.
+@pytest.mark.parametrize("M,N,K,a8", [(520, 22010, 576, False), (1000, 16448, 1088, False), (2100, 8200, 1088, False),
+                                      (1300, 12288, 1088, False), (1000, 16448, 576, True), (2100, 8200, 576, True),
+                                      (2100, 22010, 1088, True)])
+def test_ring_and_slice(M, N, K, a8):
+    say(f"ring and slice on parts of one product M={M} N={N} K={K} 8-bit={a8}")
+    rows = np.array([0, 1, M // 2, M - 1])
+    (gemm8_case if a8 else gemm_case)(M, N, K, seed=M + N, sample_rows=rows)
+
+
+@pytest.mark.parametrize("M,I,K", [(1000, 8224, 1088), (2100, 4128, 1088), (2600, 6144, 1088)])
+def test_ring_and_slice_swiglu(M, I, K):
+    say(f"ring and slice on parts of one gate/up product M={M} I={I} K={K}")
+    swiglu_case(M, I, K, seed=M + I, sample_rows=np.arange(0, M, 97))
 
 
 @pytest.mark.parametrize("M,N,ld,off", [(17, 130, 131, 1), (33, 66, 70, 2), (5, 64, 64, 0), (48, 67, 72, 4)])
