@@ -126,8 +126,7 @@ sq_status sq_had_quant_act(const void* x, int64_t M, int64_t K, int64_t ldx,
  *              S of a random Hadamard matrix S H (Sec. 2.2), so that each block of n = a*b
  *              elements is multiplied by S (H_a (x) S_b) / sqrt(n); element i of a block is
  *              multiplied by signs[i] first.  Entries are +1 or -1 (only their sign is read:
- *              negative = -1).  NULL for none.  Any alignment; the matrix-core kernels take
- *              8-byte aligned arrays, others go to the generic kernel.
+ *              negative = -1).  NULL for none.  Any alignment.
  *   clip       range clipping ratio r, 0 < r <= 1 (App. A "Quantization choice"): each group
  *              is quantized over [r min, r max] (each end rounded to fp32), so
  *              alpha = fl(fl(r max) - fl(r min)) / L, beta = fl(r min), and codes of values

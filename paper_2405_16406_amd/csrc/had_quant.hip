@@ -384,7 +384,7 @@ hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
     if (nch <= 512 * 4) return launch(quant_rows_identity<8, 4>, grid, dim3(512), 0, stream, a);
     return launch(quant_rows_identity<8, 8>, grid, dim3(512), 0, stream, a);
   }
-  const hipError_t e = launch_had_quant_kron(a, stream);
+  const hipError_t e = launch_had_quant_rows(a, stream);
   if (e != hipErrorNotSupported) return e;
   return launch_generic(had_quant_act_generic, a, stream);
 }
@@ -398,7 +398,7 @@ hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream) {
     if (nch <= 512 * 4) return launch(pack_rows_identity<8, 4>, grid, dim3(512), 0, stream, a);
     return launch(pack_rows_identity<8, 8>, grid, dim3(512), 0, stream, a);
   }
-  const hipError_t e = launch_pack_kron(a, stream);
+  const hipError_t e = launch_pack_rows(a, stream);
   if (e != hipErrorNotSupported) return e;
   return launch_generic(pack_w4_generic, a, stream);
 }

@@ -36,11 +36,14 @@ struct RotQuantArgs {
 
 // Rotation + asymmetric per-group 4- or 8-bit quantization of activation rows.
 hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream);
-// Fast path for K = a*b rows with a registered dense order, per-token 4-bit groups;
+// Fast path for K = a*b rows with a registered dense order, per-token groups;
 // hipErrorNotSupported when it does not apply.
-hipError_t launch_had_quant_kron(const RotQuantArgs& a, hipStream_t stream);
+hipError_t launch_had_quant_rows(const RotQuantArgs& a, hipStream_t stream);
 // The same for weight rows (symmetric codes, row sums); hipErrorNotSupported likewise.
-hipError_t launch_pack_kron(const RotQuantArgs& a, hipStream_t stream);
+hipError_t launch_pack_rows(const RotQuantArgs& a, hipStream_t stream);
+// Both for many rows of the 172 x 64 order (K == 172 * 64, H given, group == K).
+hipError_t launch_had_quant_pair(const RotQuantArgs& a, hipStream_t stream);
+hipError_t launch_pack_pair(const RotQuantArgs& a, hipStream_t stream);
 // Rotation + symmetric per-row 4-bit quantization of weight rows, with code row sums.
 hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream);
 

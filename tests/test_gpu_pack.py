@@ -29,8 +29,8 @@ def test_pack_rotated_row_counts(a, b, N):
 
 @pytest.mark.parametrize("a,b", FAST)
 def test_pack_rotated_strided_and_misaligned_factor(a, b):
-    """Rows with padding between them (NaN, never read); a factor that is not 16-byte aligned
-    takes the generic kernel: same codes up to rounding-boundary flips."""
+    """Rows with padding between them (NaN, never read), and a factor that is not 16-byte
+    aligned."""
     say(f"pack_w4 strided rows, misaligned factor a={a} b={b}")
     K, N = a * b, 21
     w = workloads.weights(workloads.rng_for(a + 5), N, K)
