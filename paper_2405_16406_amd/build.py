@@ -12,6 +12,9 @@ file.  Compile flags:
                                   fp32 op sequence rounds after every step
   -Xclang -target-feature -Xclang -packed-fp32-ops
                                   no packed fp32 VALU instructions in the device code
+  -mllvm -amdgpu-kernarg-preload-count=14
+                                  a kernel's leading scalar parameters (14 dwords) arrive in
+                                  registers with its waves; csrc/sq_internal.h says why
 
 Sanitizer build (build_sanitized): the host-only sources (argument validation, error
 state, Hadamard construction) compiled with AddressSanitizer and UndefinedBehaviorSanitizer
@@ -39,7 +42,8 @@ ASAN_LIB = os.path.join(ASAN_DIR, "libsq_asan.so")
 
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"-I{INCLUDE}", f"-I{CSRC}"]
-DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
             "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-g", "-shared-libsan"]
 

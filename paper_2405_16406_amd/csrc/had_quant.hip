@@ -209,7 +209,16 @@ pack_w4_generic(RotQuantArgs args) {
 // code store).
 template <int W, int CHMAX>
 __global__ void __launch_bounds__(64 * W)
-quant_rows_identity(RotQuantArgs args) {
+quant_rows_identity(const uint16_t* x, int64_t ldx, int K, uint8_t* q, float* alpha_out, float* beta_out, int bits, float clip,
+                    RotQuantArgs args) {
+  args.x = x;
+  args.ldx = ldx;
+  args.K = K;
+  args.q = q;
+  args.alpha = alpha_out;
+  args.beta = beta_out;
+  args.bits = bits;
+  args.clip = clip;
   constexpr int T = 64 * W;
   __shared__ float red[2 * W];
   const int64_t row = blockIdx.x;
@@ -304,7 +313,14 @@ quant_rows_identity(RotQuantArgs args) {
 // TB/s), [8192 x 28672] 113 vs 1665 us.
 template <int W, int CHMAX>
 __global__ void __launch_bounds__(64 * W)
-pack_rows_identity(RotQuantArgs args) {
+pack_rows_identity(const uint16_t* x, int64_t ldx, int K, uint8_t* q, float* alpha_out, int32_t* rowsum_out,
+                   RotQuantArgs args) {
+  args.x = x;
+  args.ldx = ldx;
+  args.K = K;
+  args.q = q;
+  args.alpha = alpha_out;
+  args.rowsum = rowsum_out;
   constexpr int T = 64 * W;
   __shared__ float red[W];
   __shared__ int red_i[W];
@@ -378,11 +394,14 @@ hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
     // chunks of 8 per thread sized to K, so that the registers (and with them the
     // resident workgroups per CU) follow the row length
     const dim3 grid(static_cast<unsigned>(a.rows));
+    auto go = [&](auto kern, int threads) {
+      return launch(kern, grid, dim3(threads), 0, stream, a.x, a.ldx, static_cast<int>(a.K), a.q, a.alpha, a.beta, a.bits, a.clip, a);
+    };
     const int64_t nch = a.K / 8;
-    if (nch <= 256 * 2) return launch(quant_rows_identity<4, 2>, grid, dim3(256), 0, stream, a);
-    if (nch <= 256 * 4) return launch(quant_rows_identity<4, 4>, grid, dim3(256), 0, stream, a);
-    if (nch <= 512 * 4) return launch(quant_rows_identity<8, 4>, grid, dim3(512), 0, stream, a);
-    return launch(quant_rows_identity<8, 8>, grid, dim3(512), 0, stream, a);
+    if (nch <= 256 * 2) return go(quant_rows_identity<4, 2>, 256);
+    if (nch <= 256 * 4) return go(quant_rows_identity<4, 4>, 256);
+    if (nch <= 512 * 4) return go(quant_rows_identity<8, 4>, 512);
+    return go(quant_rows_identity<8, 8>, 512);
   }
   const hipError_t e = launch_had_quant_rows(a, stream);
   if (e != hipErrorNotSupported) return e;
@@ -392,11 +411,14 @@ hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
 hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream) {
   if (a.a == 1 && a.b == 1 && a.signs == nullptr) {
     const dim3 grid(static_cast<unsigned>(a.rows));
+    auto go = [&](auto kern, int threads) {
+      return launch(kern, grid, dim3(threads), 0, stream, a.x, a.ldx, static_cast<int>(a.K), a.q, a.alpha, a.rowsum, a);
+    };
     const int64_t nch = a.K / 8;
-    if (nch <= 256 * 2) return launch(pack_rows_identity<4, 2>, grid, dim3(256), 0, stream, a);
-    if (nch <= 256 * 4) return launch(pack_rows_identity<4, 4>, grid, dim3(256), 0, stream, a);
-    if (nch <= 512 * 4) return launch(pack_rows_identity<8, 4>, grid, dim3(512), 0, stream, a);
-    return launch(pack_rows_identity<8, 8>, grid, dim3(512), 0, stream, a);
+    if (nch <= 256 * 2) return go(pack_rows_identity<4, 2>, 256);
+    if (nch <= 256 * 4) return go(pack_rows_identity<4, 4>, 256);
+    if (nch <= 512 * 4) return go(pack_rows_identity<8, 4>, 512);
+    return go(pack_rows_identity<8, 8>, 512);
   }
   const hipError_t e = launch_pack_rows(a, stream);
   if (e != hipErrorNotSupported) return e;

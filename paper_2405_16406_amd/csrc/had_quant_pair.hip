@@ -76,7 +76,14 @@ __device__ __forceinline__ void pair_wait(const int* flag, int target) {
 
 template <int A, int APAD, int NT, bool DBG, int BITS, bool VAR>
 __global__ void __launch_bounds__(512, 2)
-had_quant_pair(RotQuantArgs args) {
+had_quant_pair(const uint16_t* x, int64_t ldx, const int8_t* H, int64_t nrows, uint8_t* q, float* alpha_out,
+               RotQuantArgs args) {
+  args.x = x;
+  args.ldx = ldx;
+  args.H = H;
+  args.rows = nrows;
+  args.q = q;
+  args.alpha = alpha_out;
   using C = Pair<A, APAD, NT>;
   constexpr int B = C::B;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -436,7 +443,7 @@ hipError_t launch_pair(const RotQuantArgs& a, hipStream_t stream) {
   int n = 0;
   const int64_t cap = device_cus(&n) == hipSuccess ? n : 256;  // a wrong count costs rounds only
   const unsigned grid = static_cast<unsigned>(sets < cap ? sets : cap);
-  return launch(kern, dim3(grid), dim3(C::THREADS), C::LDS, stream, a);
+  return launch(kern, dim3(grid), dim3(C::THREADS), C::LDS, stream, a.x, a.ldx, a.H, a.rows, a.q, a.alpha, a);
 }
 
 template <int BITS, bool VAR>

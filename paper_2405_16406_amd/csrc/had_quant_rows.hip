@@ -73,7 +73,15 @@ struct Rows {
 // VAR: a clipping ratio and the signs S
 template <int A, int F, int MT, int BITS, bool VAR>
 __global__ void __launch_bounds__(64 * ((A * F + 31) / 32), 2)
-had_quant_rows(RotQuantArgs args) {
+had_quant_rows(const uint16_t* x, int64_t ldx, const int8_t* H, const int8_t* signs, uint8_t* q, float* alpha_out,
+               float* beta_out, RotQuantArgs args) {
+  args.x = x;
+  args.ldx = ldx;
+  args.H = H;
+  args.signs = signs;
+  args.q = q;
+  args.alpha = alpha_out;
+  args.beta = beta_out;
   constexpr bool SYM = BITS == kSym4;
   using C = Rows<A, F, MT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -357,7 +365,8 @@ hipError_t launch_rows(const RotQuantArgs& a, hipStream_t stream) {
   constexpr auto kern = had_quant_rows<A, F, MT, BITS, VAR>;
   const hipError_t init = set_max_lds<kern>(C::LDS);
   if (init != hipSuccess) return init;
-  return launch(kern, dim3(static_cast<unsigned>(a.rows)), dim3(C::THREADS), C::LDS, stream, a);
+  return launch(kern, dim3(static_cast<unsigned>(a.rows)), dim3(C::THREADS), C::LDS, stream, a.x, a.ldx, a.H, a.signs, a.q, a.alpha,
+                a.beta, a);
 }
 
 template <int A, int F, int MT>

@@ -345,7 +345,15 @@ constexpr int part_lds_bytes() {
 template <bool P16, bool FINAL, int kSplitWaves = kAttnSplitWaves, int kBatch = kAttnBatch, int WPE = 2,
           int kDepth = kAttnDepth>
 __global__ void __launch_bounds__(64 * kSplitWaves, WPE)
-attn_decode_part(AttnArgs a) {
+attn_decode_part(const uint16_t* q, const uint8_t* kq, const uint8_t* vq, int S, int H, int chunks, int chunk_batches,
+                 int grouped, uint32_t magic_ng, uint32_t magic_nc, AttnArgs a) {
+  a.q = q;
+  a.kq = kq;
+  a.vq = vq;
+  a.S = S;
+  a.H = H;
+  a.chunks = chunks;
+  a.chunk_batches = chunk_batches;
   constexpr int kChunkUnit = kSplitWaves * kBatch;
   // dynamic LDS (part_lds_bytes bytes): the waves' dims [wave][head][kDimRow], then (m, l) [wave][head]
   extern __shared__ __attribute__((aligned(16))) float split_lds[];
@@ -359,17 +367,13 @@ attn_decode_part(AttnArgs a) {
   // Workgroups go round-robin over the 8 XCDs.  When the count allows, the NG head groups of
   // one (batch, chunk) get ids equal mod 8, so they run on one XCD and the two halves of a
   // token's parameter lines (64 bytes each of a 128-byte line) come through one L2.
-  const int id = static_cast<int>(blockIdx.x), total = static_cast<int>(gridDim.x);
-  int g, bc;
-  if (NG > 1 && total % (8 * NG) == 0) {
-    g = (id / 8) % NG;
-    bc = (id / (8 * NG)) * 8 + id % 8;
-  } else {
-    g = id % NG;
-    bc = id / NG;
-  }
-  const int c = bc % NC;
-  const int64_t b = bc / NC;
+  const int id = static_cast<int>(blockIdx.x);
+  uint32_t g, bc, b32, c32;
+  div_rem(grouped ? id / 8 : id, NG, magic_ng, bc, g);
+  if (grouped) bc = bc * 8 + id % 8;
+  div_rem(bc, NC, magic_nc, b32, c32);
+  const int c = static_cast<int>(c32);
+  const int64_t b = b32;
   const int64_t h = kAttnGroupHeads * g + hh;
   const bool hok = h < a.H;
   const int64_t hq = hok ? h : a.H - 1;  // lanes past the heads run on the last head and store nothing
@@ -512,11 +516,10 @@ attn_decode_part(AttnArgs a) {
 // workgroup, so the heads spread over all CUs (0.2-0.3 us less than four waves per
 // workgroup on [8, 2048, 32, 128]).
 __global__ void __launch_bounds__(64)
-attn_decode_combine(AttnArgs a) {
+attn_decode_combine(const float* part, uint16_t* out, int NC) {
   const int lane = threadIdx.x;
   const int64_t x = blockIdx.x;  // B * H < 2^31 is checked on the host
-  const int NC = static_cast<int>(a.chunks);
-  const float* pr = a.part + x * NC * kAttnPart;
+  const float* pr = part + x * NC * kAttnPart;
   const int cl = lane < NC ? lane : NC - 1;
   const float2 ml = *reinterpret_cast<const float2*>(pr + cl * kAttnPart);
   float2 d[32];
@@ -547,7 +550,7 @@ attn_decode_combine(AttnArgs a) {
       d[j] = reinterpret_cast<const float2*>(pr + min(32 + j, NC - 1) * kAttnPart + 4)[lane];
     add32(32);
   }
-  reinterpret_cast<uint32_t*>(a.out + x * 128)[lane] =
+  reinterpret_cast<uint32_t*>(out + x * 128)[lane] =
       static_cast<uint32_t>(f2h(__fdiv_rn(A0, L))) | (static_cast<uint32_t>(f2h(__fdiv_rn(A1, L))) << 16);
 }
 
@@ -581,9 +584,12 @@ template <bool P16, bool FINAL>
 hipError_t launch_part(const AttnArgs& a, unsigned parts, hipStream_t stream) {
   constexpr auto kern = attn_decode_part<P16, FINAL>;
   constexpr int lds = part_lds_bytes<kAttnSplitWaves>();
+  const uint32_t ng = static_cast<uint32_t>((a.H + kAttnGroupHeads - 1) / kAttnGroupHeads);
   const hipError_t init = set_max_lds<kern>(lds);  // above the 64 KB default
   if (init != hipSuccess) return init;
-  return launch(kern, dim3(parts), dim3(64 * kAttnSplitWaves), lds, stream, a);
+  return launch(kern, dim3(parts), dim3(64 * kAttnSplitWaves), lds, stream, a.q, a.kq, a.vq, static_cast<int>(a.S),
+                static_cast<int>(a.H), static_cast<int>(a.chunks), static_cast<int>(a.chunk_batches),
+                ng > 1 && parts % (8 * ng) == 0 ? 1 : 0, div_magic(ng), div_magic(static_cast<uint32_t>(a.chunks)), a);
 }
 }  // namespace
 
@@ -594,7 +600,8 @@ hipError_t launch_attn_decode_split(const AttnArgs& a, hipStream_t stream) {
     return a.param16 ? launch_part<true, true>(a, parts, stream) : launch_part<false, true>(a, parts, stream);
   hipError_t e = a.param16 ? launch_part<true, false>(a, parts, stream) : launch_part<false, false>(a, parts, stream);
   if (e != hipSuccess) return e;
-  return launch(attn_decode_combine, dim3(static_cast<unsigned>(a.B * a.H)), dim3(64), 0, stream, a);
+  return launch(attn_decode_combine, dim3(static_cast<unsigned>(a.B * a.H)), dim3(64), 0, stream, a.part, a.out,
+                static_cast<int>(a.chunks));
 }
 
 hipError_t launch_attn_decode_kv4(const AttnArgs& a, hipStream_t stream) {

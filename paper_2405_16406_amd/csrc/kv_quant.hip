@@ -171,7 +171,15 @@ __device__ __forceinline__ void quant_store(const float (&e)[32], int j, float s
 // transform.
 template <bool EARLY, int BITS, bool P16>
 __global__ void __launch_bounds__(kThreads)
-qk_had_kvquant_v2(KvArgs a) {
+qk_had_kvquant_v2(const uint16_t* q_in, const uint16_t* k_in, const uint16_t* v_in, int64_t groups, uint16_t* q_rot,
+                  uint8_t* kq, uint8_t* vq, KvArgs a) {
+  a.q = q_in;
+  a.k = k_in;
+  a.v = v_in;
+  a.groups = groups;
+  a.q_rot = q_rot;
+  a.kq = kq;
+  a.vq = vq;
   const int64_t grp = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) / 4;
   const int j = threadIdx.x & 3;
   if (grp >= a.groups) return;  // the 4 lanes of a group leave together
@@ -226,8 +234,8 @@ hipError_t launch_qk_had_kvquant(const KvArgs& a, hipStream_t stream) {
   const dim3 grid(blocks), block(kThreads);
   auto go = [&](auto early_c, auto p16_c) -> hipError_t {
     constexpr bool E = decltype(early_c)::value, P = decltype(p16_c)::value;
-    return a.bits == 8 ? launch(qk_had_kvquant_v2<E, 8, P>, grid, block, 0, stream, a)
-                       : launch(qk_had_kvquant_v2<E, 4, P>, grid, block, 0, stream, a);
+    return launch(a.bits == 8 ? qk_had_kvquant_v2<E, 8, P> : qk_had_kvquant_v2<E, 4, P>, grid, block, 0, stream, a.q, a.k,
+                  a.v, a.groups, a.q_rot, a.kq, a.vq, a);
   };
   using T = std::true_type;
   using N = std::false_type;

@@ -92,4 +92,13 @@ __device__ __forceinline__ int wave_sum(int v) {
   return static_cast<int>(wave_all(static_cast<uint32_t>(v), [](uint32_t a, uint32_t b) { return a + b; }));
 }
 
+// floor(x / d) and the remainder, with magic = floor(2^32 / d) + 1 from the host (32 bits; 0 for
+// d == 1).  x magic / 2^32 exceeds x / d by at most x / 2^32: its floor is at most one too many.
+inline uint32_t div_magic(uint32_t d) { return d == 1 ? 0u : static_cast<uint32_t>((uint64_t{1} << 32) / d + 1); }
+__device__ __forceinline__ void div_rem(uint32_t x, uint32_t d, uint32_t magic, uint32_t& quot, uint32_t& rem) {
+  quot = magic ? static_cast<uint32_t>((static_cast<uint64_t>(x) * magic) >> 32) : x;
+  if (quot * d > x) --quot;
+  rem = x - quot * d;
+}
+
 }  // namespace sq

@@ -29,16 +29,16 @@ namespace {
 // Tile order.  Consecutive workgroup ids go to different XCDs (round robin over 8), so each
 // XCD is given a contiguous range of tile ids; within it the tile walks M fastest, so the
 // CUs of one XCD share weight (B) tiles in their L2 and each weight tile is read from HBM
-// about once.  Grid: x = tiles along N, y = tiles along M.
-__device__ __forceinline__ void tile_origin(int bm, int bn, int64_t& m0, int64_t& n0) {
-  const int tiles_m = gridDim.y;
-  const int total = gridDim.x * gridDim.y;
-  const int bid = blockIdx.y * gridDim.x + blockIdx.x;
+// about once.
+__device__ __forceinline__ void tile_origin(int bm, int bn, int tiles_m, int total, uint32_t magic, int64_t& m0, int64_t& n0) {
+  const int bid = blockIdx.x;
   const int q8 = total / 8, r8 = total % 8;
   const int xcd = bid % 8, idx = bid / 8;
   const int tile = xcd < r8 ? xcd * (q8 + 1) + idx : r8 * (q8 + 1) + (xcd - r8) * q8 + idx;
-  m0 = static_cast<int64_t>(tile % tiles_m) * bm;
-  n0 = static_cast<int64_t>(tile / tiles_m) * bn;
+  uint32_t tn, tm;
+  div_rem(tile, tiles_m, magic, tn, tm);
+  m0 = static_cast<int64_t>(tm) * bm;
+  n0 = static_cast<int64_t>(tn) * bn;
 }
 
 // Epilogue of the ring kernel.  Its MFMAs take the weights as the A operand, so each 32 x 32
@@ -357,7 +357,13 @@ struct RingLds {
 
 template <int WAVES_M, int WAVES_N, int TM, int TN, int NS, int WPE, bool A8 = false>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WPE)
-w4a4_gemm_ring(GemmArgs g) {
+w4a4_gemm_ring(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K, int tiles_m, int tiles, uint32_t magic,
+               GemmArgs g) {
+  g.xq = xq;
+  g.wq = wq;
+  g.M = M;
+  g.N = N;
+  g.K = K;
   using R = Ring<WAVES_M, WAVES_N, TM, TN, NS, A8>;
   using L = RingLds<WAVES_M, WAVES_N, TM, TN, NS, A8>;
   using SC = RingScales<R::BM, R::BN>;
@@ -367,7 +373,7 @@ w4a4_gemm_ring(GemmArgs g) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint8_t* const ring = lds;
   int64_t m0, n0;
-  tile_origin(R::BM, R::BN, m0, n0);
+  tile_origin(R::BM, R::BN, tiles_m, tiles, magic, m0, n0);
   const int wm = (wave / WAVES_N) * TM;  // first 32-row group of this wave in the tile
   const int wn = (wave % WAVES_N) * TN;
   const uint32_t KB = static_cast<uint32_t>(g.K / 2);
@@ -551,8 +557,12 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
   constexpr auto kern = w4a4_gemm_ring<WM, WN, TM, TN, NS, WPE, A8>;
   const hipError_t init = set_max_lds<kern>(LDS);
   if (init != hipSuccess) return init;
-  const dim3 grid(static_cast<unsigned>((g.N + R::BN - 1) / R::BN), static_cast<unsigned>((g.M + R::BM - 1) / R::BM));
-  return launch(kern, grid, dim3(R::THREADS), LDS, stream, g);
+  // the 31-bit operand ranges (fits_ring) bound M and N, and with them the tiles, far below 2^31
+  const int64_t tn = (g.N + R::BN - 1) / R::BN, tm = (g.M + R::BM - 1) / R::BM;
+  if (tn * tm >= (int64_t{1} << 31)) return hipErrorInvalidConfiguration;
+  return launch(kern, dim3(static_cast<unsigned>(tn * tm)), dim3(R::THREADS), LDS, stream, g.xq, g.wq, g.M, g.N,
+                static_cast<int>(g.K), static_cast<int>(tm), static_cast<int>(tn * tm),
+                div_magic(static_cast<uint32_t>(tm)), g);
 }
 
 // Gate/up products are taken where the byte offsets of the kernels they were first built on
