@@ -10,10 +10,10 @@ namespace sq {
 
 enum GemmFamily { kW4A4 = 0, kW4A4Swiglu = 1, kW4A8 = 2 };
 
-// A tile of the slice kernel (gemm_slice.h): 16 nb weight rows x 16 mb tokens, ns ring slots
-// per wave of seg packed bytes per row.
+// A tile of the slice kernel (gemm_slice.h): 16 nb weight rows x 16 mb tokens, K split over
+// `waves` waves, ns ring slots per wave of seg packed bytes per row.
 struct SlicePlan {
-  int nb, mb, ns, seg;
+  int nb, mb, waves, ns, seg;
   float us;  // its estimated time
 };
 
@@ -39,9 +39,31 @@ constexpr bool slice_has(GemmFamily f, int nb, int mb) {
 //   [48 x 4096] x [28672 x 4096], 4 x 3, 448                       16.2 | 14.2 | 13.8 | 13.9
 //   [512 x 4096] x [22016 x 4096], 4 x 4, 2752                     -    | 57.4 | -    | 53.2
 //   [16 x 8192] x [57344 x 8192], 2 x 1, 1792                      42.6 | -    | 46.4 | -
-inline void slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, int* ns, int* seg) {
+// Eight waves with one short slot each, two per SIMD, instead of four waves with two slots:
+// one wave's expansion of the codes runs under the other's products.  That pays in one round
+// of tiles where a wave has enough products (12 blocks) or the few stages of a short K are
+// mostly start and end; over a long K whole cache lines matter more, SiLU pairs gain nothing
+// and 8-bit 4 x 4 tiles lose 1 - 3 %.  Time against four waves, K = 4096 | 8192 | 11008 | 14336 |
+// 28672 (geometric means over 1 - 13 products each):
+//   4-bit  1 x 1 .94 | - | 1.13 | 1.17 | -           2 x 2 .87 | 1.01 | 1.04 | 1.05 | 1.23
+//          4 x 4 .92 | .94 | .90 | .92 | 1.13        4 x 5 .94 | .98 | .94 | .96 | 1.21
+//          8 x 4 .93 | .96 | .94 | .93 | .96         4 x 2 .98 | 1.02 | 1.02 | 1.03 | 1.24
+//   8-bit  2 x 1 .88 | .95 | 1.00 | 1.02 | 1.14      4 x 3 .96 | .95 | .93 | .94 | .96
+//          6 x 3 .95 | .94 | .95 | .94 | 1.01        4 x 4 1.00 | 1.04 | 1.02 | 1.01 | 1.01
+// ([300 x 11008] x [4096 x 11008] 4 x 5: 19.4 to 17.8 us; [24 x 4096] x [4096 x 4096] 2 x 1: 4.1
+// to 3.5.)
+inline bool slice_eight_waves(GemmFamily f, int nb, int mb, int64_t K) {
+  if (f == kW4A4Swiglu || K >= 16384) return false;
+  return K < 8192 || (nb * mb >= 12 && !(f == kW4A8 && nb == 4 && mb == 4));
+}
+inline void slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, int* waves, int* ns, int* seg) {
   const bool a8 = f == kW4A8;
-  if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) {
+  *waves = 4;
+  if (one_round && slice_eight_waves(f, nb, mb, K)) {
+    *waves = 8;
+    *ns = 1;
+    *seg = 64;
+  } else if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) {
     *ns = K >= 8192 ? 2 : 1;
     *seg = 128;
   } else if (one_round) {
@@ -89,7 +111,7 @@ inline double slice_us(GemmFamily f, const GemmArgs& g, int shape, int cus) {
 }
 
 inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
-  SlicePlan best{0, 0, 0, 0, 0.0f};
+  SlicePlan best{0, 0, 0, 0, 0, 0.0f};
   double us = 0.0;
   for (int s = 0; s < kSliceShapes; ++s) {
     const int nb = kSliceShape[s][0], mb = kSliceShape[s][1];
@@ -103,7 +125,7 @@ inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
   }
   best.us = static_cast<float>(us);
   const int64_t tiles = ((g.M + 16 * best.mb - 1) / (16 * best.mb)) * ((g.N + 16 * best.nb - 1) / (16 * best.nb));
-  slice_ring(f, best.nb, best.mb, g.K, tiles <= cus, &best.ns, &best.seg);
+  slice_ring(f, best.nb, best.mb, g.K, tiles <= cus, &best.waves, &best.ns, &best.seg);
   return best;
 }
 

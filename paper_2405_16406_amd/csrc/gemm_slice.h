@@ -184,7 +184,12 @@ w4_gemm_slice(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K,
 
   issue(std::integral_constant<int, 0>{}, 0);
   // epilogue scales: fetched behind the first stage's copies (clamped indices, no branch around
-  // a load), kept until the last products
+  // a load).  Small tiles, and eight waves (one workgroup per CU in any case), stage them after
+  // the products, off the first stage's path (4 x 3 tiles, [48 x 4096] x [28672 x 4096] with SiLU:
+  // 13.2 against 13.7 us; 4 x 5, [300 x 11008] x [4096 x 11008]: 17.4 against 18.9); larger ones
+  // of four waves when that stage has landed, since held through the products they cost a
+  // workgroup per CU ([320 x 8192] x [57344 x 8192]: 167 against 180).
+  constexpr bool kLate = NB * MB <= 12 || W == 8;
   constexpr int SPT = (S::SCALES + S::THREADS - 1) / S::THREADS;
   float fxa[SPT], fxb[SPT], fwa[SPT];
   int32_t frs[SPT];
@@ -204,6 +209,28 @@ w4_gemm_slice(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K,
     fbi[u] = bp[nc];
   }
   static_for<NS - 1>([&](auto pc) { issue(std::integral_constant<int, decltype(pc)::value + 1>{}, decltype(pc)::value + 1); });
+
+  auto stage_scales = [&] {
+#pragma unroll
+    for (int u = 0; u < SPT; ++u) {
+      const int x = static_cast<int>(threadIdx.x) + u * S::THREADS;
+      const int t = x < 2 * S::BM ? 0 : x - 2 * S::BM;
+      const bool mok = m0 + x % S::BM < g.M, nok = col_of(t % S::BN) < g.N;
+      float v;
+      if (x < S::BM)
+        v = mok ? __fmul_rn(fxa[u], 0.0625f) : 0.0f;
+      else if (x < 2 * S::BM)
+        v = mok ? (A8 ? __fmaf_rn(128.0f, fxa[u], fxb[u]) : fxb[u]) : 0.0f;
+      else if (t < S::BN)
+        v = nok ? fwa[u] : 0.0f;
+      else if (t < 2 * S::BN)
+        v = nok ? static_cast<float>(frs[u]) : 0.0f;
+      else
+        v = nok && g.bias ? h2f(fbi[u]) : 0.0f;
+      if (x < S::SCALES) scales[x] = v;
+    }
+  };
+  if constexpr (!kLate) stage_scales();
 
   for (int t0 = 0; t0 < T; t0 += NS) {
     static_for<NS>([&](auto pc) {
@@ -264,24 +291,7 @@ w4_gemm_slice(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K,
       }
     });
   }
-#pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    const int x = static_cast<int>(threadIdx.x) + u * S::THREADS;
-    const int t = x < 2 * S::BM ? 0 : x - 2 * S::BM;
-    const bool mok = m0 + x % S::BM < g.M, nok = col_of(t % S::BN) < g.N;
-    float v;
-    if (x < S::BM)
-      v = mok ? __fmul_rn(fxa[u], 0.0625f) : 0.0f;
-    else if (x < 2 * S::BM)
-      v = mok ? (A8 ? __fmaf_rn(128.0f, fxa[u], fxb[u]) : fxb[u]) : 0.0f;
-    else if (t < S::BN)
-      v = nok ? fwa[u] : 0.0f;
-    else if (t < 2 * S::BN)
-      v = nok ? static_cast<float>(frs[u]) : 0.0f;
-    else
-      v = nok && g.bias ? h2f(fbi[u]) : 0.0f;
-    if (x < S::SCALES) scales[x] = v;
-  }
+  if constexpr (kLate) stage_scales();
   wait_vm_lgkm0<0>();  // copies past the run (zeros) have landed
   __syncthreads();     // every wave is done with its ring; the scales are in place
 
@@ -359,13 +369,11 @@ w4_gemm_slice(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K,
   });
 }
 
-constexpr int kSliceWaves = 4;
-
-template <int NB, int MB, int NS, int SEG, GemmFamily F>
+template <int NB, int MB, int W, int NS, int SEG, GemmFamily F>
 hipError_t launch_slice(const GemmArgs& g, hipStream_t stream) {
   constexpr bool A8 = F == kW4A8, SW = F == kW4A4Swiglu;
-  using S = Slice<NB, MB, kSliceWaves, NS, SEG, A8>;
-  constexpr auto kern = w4_gemm_slice<NB, MB, kSliceWaves, NS, SEG, A8, SW>;
+  using S = Slice<NB, MB, W, NS, SEG, A8>;
+  constexpr auto kern = w4_gemm_slice<NB, MB, W, NS, SEG, A8, SW>;
   const hipError_t init = set_max_lds<kern>(S::LDS);
   if (init != hipSuccess) return init;
   const int64_t tn = SW ? (g.N / 32 + NB / 2 - 1) / (NB / 2) : (g.N + S::BN - 1) / S::BN;
@@ -385,13 +393,15 @@ hipError_t launch_slice_plan(const GemmArgs& g, const SlicePlan& p, hipStream_t 
     if constexpr (slice_has(F, nb, mb)) {
       if (p.nb != nb || p.mb != mb) return;
       constexpr bool a8 = F == kW4A8;
-      if (p.seg == 128) {
+      if (p.waves == 8) {
+        if constexpr (F != kW4A4Swiglu) e = launch_slice<nb, mb, 8, 1, 64, F>(g, stream);
+      } else if (p.seg == 128) {
         if constexpr (nb + mb <= (a8 ? 4 : 9))
-          if (p.ns == 2) e = launch_slice<nb, mb, 2, 128, F>(g, stream);
+          if (p.ns == 2) e = launch_slice<nb, mb, 4, 2, 128, F>(g, stream);
         if constexpr (nb + mb <= (a8 ? 5 : 9))
-          if (p.ns == 1) e = launch_slice<nb, mb, 1, 128, F>(g, stream);
+          if (p.ns == 1) e = launch_slice<nb, mb, 4, 1, 128, F>(g, stream);
       } else {
-        e = p.ns == 2 ? launch_slice<nb, mb, 2, 64, F>(g, stream) : launch_slice<nb, mb, 1, 64, F>(g, stream);
+        e = p.ns == 2 ? launch_slice<nb, mb, 4, 2, 64, F>(g, stream) : launch_slice<nb, mb, 4, 1, 64, F>(g, stream);
       }
     }
   });

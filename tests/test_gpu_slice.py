@@ -57,6 +57,24 @@ def test_w4a8_slice(M, N, K):
     gemm8_case(M, N, K, seed=M + 5 * N + K, bias=(M + N) % 3 != 0)
 
 
+# The other tiles, wave counts, ring depths and segment lengths of the three families: four waves
+# in several rounds and over a long K, eight waves elsewhere ("swiglu": rows of gate alone).
+FORMS = [(2828, 33, 8640, "w4a4"), (98, 2952, 9536, "w4a4"), (107, 6031, 17344, "w4a4"), (169, 7901, 17216, "w4a4"),
+      (1640, 1810, 192, "w4a4"), (3681, 386, 192, "w4a4"), (1, 4480, 1344, "swiglu"), (17, 4256, 1344, "swiglu"),
+      (33, 4352, 2112, "swiglu"), (33, 2208, 192, "swiglu"), (1, 8352, 448, "swiglu"), (49, 3072, 16704, "swiglu"),
+      (37, 8384, 576, "swiglu"), (402, 2336, 192, "swiglu"), (97, 3488, 17472, "swiglu"), (49, 4512, 192, "swiglu"),
+      (92, 4192, 192, "swiglu"), (3663, 544, 192, "swiglu"), (3269, 288, 192, "swiglu"), (1, 4451, 2880, "w4a8"),
+      (19, 9492, 3136, "w4a8"), (17, 6603, 8640, "w4a8"), (34, 6421, 8384, "w4a8"), (51, 9699, 8256, "w4a8"),
+      (65, 12375, 192, "w4a8")]
+
+
+@pytest.mark.parametrize("M,N,K,family", FORMS)
+def test_slice_forms(M, N, K, family):
+    say(f"{family} slice form M={M} N={N} K={K}")
+    case = dict(w4a4=gemm_case, swiglu=swiglu_case, w4a8=gemm8_case)[family]
+    case(M, N, K, seed=M + N + K, sample_rows=np.unique([0, M // 2, M - 1]))
+
+
 # Products that fill whole rounds of ring tiles and leave a rest for the slice kernel.  The
 # accumulators' call runs as one kernel, so its outputs check the split one's bit for bit.
 @pytest.mark.parametrize("M,N,K,a8", [(520, 22010, 576, False), (1000, 16448, 1088, False), (2100, 8200, 1088, False),
