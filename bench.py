@@ -113,6 +113,8 @@ def entry(ms, work, kind, bound=None):
 # ---------------------------------------------------------------- measured HBM traffic
 
 def source_hash(path):
+    if not os.path.exists(path):  # the source the counters were taken on is gone
+        return None
     with open(path, "rb") as f:
         return hashlib.sha256(f.read()).hexdigest()[:16]
 
@@ -124,13 +126,13 @@ def source_hash(path):
 TRAFFIC_MAP = {
     "c2/kv_quant": ("step", "qk_had_kvquant_v2<false, 4, false>", 262144),
     "c2/act_quant": ("step", "quant_rows_identity<4, 2>", 524288),
-    "c2/gate_up_swiglu": ("step", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, 1, false>", 352256),
+    "c2/gate_up_swiglu": ("step", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, false>", 352256),
     "c2/r4_had_quant": ("step", "had_quant_pair<172, 176, 6, false, 4, false>", 131072),
-    "c2/down_gemm": ("step", "w4a4_gemm_ring<2, 4, 2, 2, 3, 1, 1, false>", 131072),
+    "c2/down_gemm": ("step", "w4a4_gemm_ring<2, 4, 2, 2, 3, 1, false>", 131072),
     "c3/act_quant": ("c3", "quant_rows_identity<4, 2>", 1048576),
-    "c3/gate_up_swiglu": ("c3", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, 1, false>", 917504),
-    "c3/r4_had_quant": ("c3", "had_quant_lines<28, 8, 7, false, 4, false>", 229376),
-    "c3/down_gemm": ("c3", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, 1, false>", 131072),
+    "c3/gate_up_swiglu": ("c3", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, false>", 917504),
+    "c3/r4_had_quant": ("c3", "had_quant_rows<28, 4, 4, 4, false>", 1048576),
+    "c3/down_gemm": ("c3", "w4a4_gemm_ring<2, 4, 4, 2, 4, 1, false>", 131072),
     "c4/kv_quant": ("c4", "qk_had_kvquant_v2<true, 4, false>", 2097152),
     "c4/attn_decode": ("c4", "attn_decode_kv4<false>", 262144),
     # two kernels (on 256 CUs: 16 chunks x 2 groups of 16 heads x 8 batches of 8 waves,
@@ -140,7 +142,7 @@ TRAFFIC_MAP = {
 }
 for _m, _g in ((1, 256), (8, 2048), (16, 4096)):  # the decode sizes share the GEMM launch shapes
     TRAFFIC_MAP[f"c5m{_m}/act_quant"] = ("c5", "quant_rows_identity<4, 4>", _g)
-    TRAFFIC_MAP[f"c5m{_m}/r4_had_quant"] = ("c5", "had_quant_lines<28, 16, 14, false, 4, false>", 896 * _m)
+    TRAFFIC_MAP[f"c5m{_m}/r4_had_quant"] = ("c5", "had_quant_rows<28, 4, 8, 4, false>", 256 * _m)
     # M = 1: the dot-product kernel, 8 waves on each of the 256 CUs; M = 8 and 16: the
     # LDS-streaming kernel (gate/up: 256 workgroups of 7 gate/up block pairs; down: 256 of 2
     # blocks)
@@ -708,8 +710,9 @@ for _c in ("FETCH_SIZE", "WRITE_SIZE"):
 PROFILE_COMMANDS["summary"] = "python3 bench.py --summarize DIR"
 
 SOURCE_OF = {"qk_had_kvquant": "kv_quant.hip", "quant_rows_identity": "had_quant.hip",
-             "had_quant_act_generic": "had_quant.hip", "had_quant_": "had_quant_kron.hip",
-             "w4a4_gemm": "w4a4_gemm.hip", "w4a4_gemv": "w4a4_gemm.hip", "attn_decode": "kv_attn.hip"}
+             "had_quant_act_generic": "had_quant.hip", "had_quant_rows": "had_quant_rows.hip",
+             "had_quant_pair": "had_quant_pair.hip", "w4a4_gemm": "w4a4_gemm.hip", "w4_gemm_slice": "gemm_slice.h",
+             "attn_decode": "kv_attn.hip"}
 
 
 def _csv_rows(d, pattern):
@@ -724,10 +727,7 @@ def _csv_rows(d, pattern):
 
 def _short(name):
     name = name.replace("(anonymous namespace)::", "").replace("sq::", "")
-    for cut in ("(sq::", "(RotQuantArgs", "(GemmArgs", "(KvArgs", "(AttnArgs", "(long", "(int"):
-        if cut in name:
-            name = name[:name.index(cut)]
-    return name.replace("void ", "").strip()
+    return name.split("(")[0].replace("void ", "").strip()
 
 
 def _pmc_per_kernel(rows, counter):
