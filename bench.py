@@ -143,13 +143,9 @@ TRAFFIC_MAP = {
 for _m, _g in ((1, 256), (8, 2048), (16, 4096)):  # the decode sizes share the GEMM launch shapes
     TRAFFIC_MAP[f"c5m{_m}/act_quant"] = ("c5", "quant_rows_identity<4, 4>", _g)
     TRAFFIC_MAP[f"c5m{_m}/r4_had_quant"] = ("c5", "had_quant_rows<28, 4, 8, 4, false>", 256 * _m)
-    # M = 1: the dot-product kernel, 8 waves on each of the 256 CUs; M = 8 and 16: the
-    # LDS-streaming kernel (gate/up: 256 workgroups of 7 gate/up block pairs; down: 256 of 2
-    # blocks)
-    TRAFFIC_MAP[f"c5m{_m}/gate_up_swiglu"] = (("c5", "w4a4_gemv<1, true, false>", 131072) if _m == 1 else
-                                              ("c5", "w4a4_gemm_stream<256, 2, true, false>", 131072))
-    TRAFFIC_MAP[f"c5m{_m}/down_gemm"] = (("c5", "w4a4_gemv<1, false, false>", 131072) if _m == 1 else
-                                         ("c5", "w4a4_gemm_stream<256, 2, false, false>", 131072))
+    # 2 x 1 blocks of 4 waves: 1792 tiles of gate/up block pairs, 256 of the down projection
+    TRAFFIC_MAP[f"c5m{_m}/gate_up_swiglu"] = ("c5", "w4_gemm_slice<2, 1, 4, 2, 128, false, true>", 458752)
+    TRAFFIC_MAP[f"c5m{_m}/down_gemm"] = ("c5", "w4_gemm_slice<2, 1, 4, 2, 128, false, false>", 65536)
 
 
 def measured_traffic(key):
