@@ -23,7 +23,7 @@
 //     are transformed, and written to their slots once both waves of a row have read it;
 //   * one lane-half stage by v_permlane32_swap; per-row min/max (the two waves of a row meet
 //     in LDS); codes use one fma per value and v_cvt_pk_u8_f32 (round half to even), which
-//     can move a code by one only on a rounding boundary;
+//     can move a code by one only within 2^-12 of a rounding boundary (kMaxOffset);
 //   * the two waves of a row synchronise with each other only (progress counters in LDS),
 //     never with the other rows' waves, so each pair starts as soon as its own row is in.
 // Bound by vector issue, for weight rows too.  Measured on MI355X (us): activations 1024 rows
@@ -393,10 +393,32 @@ had_quant_pair(const uint16_t* x, int64_t ldx, const int8_t* H, int64_t nrows, u
       const float a_u = __fdiv_rn(r_u, BITS == 8 ? 255.0f : 15.0f);
       const bool cst = __fmul_rn(a_u, s_n) < kMinNormal;
       const float inv_u = cst ? 0.0f : __fdiv_rn(1.0f, a_u);
-      const float nb = -__fmul_rn(mn, inv_u);
+      float nb = -__fmul_rn(mn, inv_u);
       if (valid && h == 0 && lane == 0) {
         args.alpha[row] = cst ? 1.0f : __fmul_rn(a_u, s_n);
         args.beta[row] = __fmul_rn(mn, s_n);
+      }
+      if constexpr (DBG) {
+#pragma unroll
+        for (int nt = 0; nt < C::NTW; ++nt) {
+          const int ja = (h * C::NTW + nt) * 32 + c;
+          if (valid && ja < A) {
+#pragma unroll
+            for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+              for (int j = 0; j < 16; ++j)
+                args.dbg[row * C::K + ja * B + mt * 32 + 16 * g + j] = __fmul_rn(acc[mt][nt][j], s_n);
+          }
+        }
+      }
+      if (fabsf(nb) > kMaxOffset) {  // the same for the whole row
+#pragma unroll
+        for (int mt = 0; mt < C::MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < C::NTW; ++nt)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[mt][nt][j] = __fsub_rn(acc[mt][nt][j], mn);
+        nb = 0.0f;
       }
 
       // ---- codes: lane (c, g) holds i_b = mt*32 + 16g + j (j = 0..15) of column j_a: bytes
@@ -419,12 +441,6 @@ had_quant_pair(const uint16_t* x, int64_t ldx, const int8_t* H, int64_t nrows, u
             const uint32_t w0 = code_word<VAR, BITS>(acc[mt][nt], 0, inv_u, nb, none);
             const uint32_t w1 = code_word<VAR, BITS>(acc[mt][nt], 8, inv_u, nb, none);
             if (valid && ja < A) *reinterpret_cast<uint2*>(qrow + pos / 2) = make_uint2(w0, w1);
-          }
-          if constexpr (DBG) {
-            if (valid && ja < A) {
-#pragma unroll
-              for (int j = 0; j < 16; ++j) args.dbg[row * C::K + pos + j] = __fmul_rn(acc[mt][nt][j], s_n);
-            }
           }
         }
       }

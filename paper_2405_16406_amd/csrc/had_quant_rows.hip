@@ -31,7 +31,7 @@
 //     word i % 4 of the 8-byte segment addressed by lane 4 e + i / 4.
 //   * Codes are one fma per value in the unscaled domain and v_cvt_pk_u8_f32 (rounds half to
 //     even), the 1/sqrt(K) scale folded into alpha and beta; a code can differ from eq. 1's
-//     steps only where the value sits on a rounding boundary.
+//     steps only where its argument is within 2^-12 of a rounding boundary (kMaxOffset).
 // What bounds it: a single row its own chain of load, products, butterflies, reduction and
 // codes; many rows the vector issue (about 14 operations per value) and the row copies.
 // Measured on MI355X, 4-bit codes (us; before: F = 8 or 16 with 7 or 14 waves and persistent
@@ -296,6 +296,15 @@ had_quant_rows(const uint16_t* x, int64_t ldx, const int8_t* H, const int8_t* si
     mx = fmaxf(mx, red[C::NT + v]);
   }
 
+  if constexpr (!SYM) {
+    if (args.dbg && real) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          args.dbg[row * C::K + n * C::COLS + mt * 32 + 16 * g + j] = __fmul_rn(acc[mt][j], s_n);
+    }
+  }
   // ---- eq. 1; asymmetric: in the unscaled domain, the reported alpha and beta carry the
   // 1/sqrt(K) scale
   float alpha, beta = 0.0f, scale, off;
@@ -314,6 +323,13 @@ had_quant_rows(const uint16_t* x, int64_t ldx, const int8_t* H, const int8_t* si
     off = -__fmul_rn(mn, scale);
     alpha = cst ? 1.0f : __fmul_rn(a_u, s_n);
     beta = __fmul_rn(mn, s_n);
+    if (fabsf(off) > kMaxOffset) {  // the same for the whole row
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[mt][j] = __fsub_rn(acc[mt][j], mn);
+      off = 0.0f;
+    }
   }
   // codes of line n, columns 32 mt + 16 g ..
   uint8_t* const qrow = args.q + row * (BITS == 8 ? C::K : C::K / 2);
@@ -337,13 +353,6 @@ had_quant_rows(const uint16_t* x, int64_t ldx, const int8_t* H, const int8_t* si
     if (threadIdx.x == 0) {
       args.alpha[row] = alpha;
       args.beta[row] = beta;
-    }
-    if (args.dbg && real) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-          args.dbg[row * C::K + n * C::COLS + mt * 32 + 16 * g + j] = __fmul_rn(acc[mt][j], s_n);
     }
   } else {
     const int sum = wave_sum(real ? static_cast<int>(sum8) - 8 * 16 * MT : 0);

@@ -30,6 +30,13 @@ __device__ __forceinline__ float code_arg(float t) {
   return t;
 }
 
+// Codes are one fma, t = v (1 / alpha) + off with off = -fl(min / alpha): the rounding of off
+// shifts a row's arguments by up to |off| 2^-24 of a step.  Rows whose range is so small against
+// their values that |off| exceeds this bound subtract the minimum first (eq. 1's own steps, off
+// becomes 0); with the others no argument moves by more than 2^-12 of a step, so it stays below
+// 15.5 and 4-bit codes need no clamp, whatever the row.
+constexpr float kMaxOffset = 4096.0f;
+
 // Eight values' 4-bit codes, even positions in the low nibbles; kSym4: two's complement, and
 // the sum of (code + 8) added to sum8
 template <bool VAR, int BITS>
