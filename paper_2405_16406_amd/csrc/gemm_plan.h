@@ -163,7 +163,36 @@ inline GemmArgs weight_rows(GemmFamily f, const GemmArgs& g, int64_t r0, int64_t
   s.rs = g.rs + r0;
   s.bias = g.bias ? g.bias + r0 : nullptr;
   s.y = g.y + (f == kW4A4Swiglu ? r0 / 2 : r0);
+  s.dbg_acc = g.dbg_acc ? g.dbg_acc + r0 : nullptr;  // of one token: the rows keep the product's stride
   return s;
+}
+
+// The tokens [m0, m1) of a product.
+inline GemmArgs token_rows(GemmFamily f, const GemmArgs& g, int64_t m0, int64_t m1) {
+  GemmArgs s = g;
+  s.M = m1 - m0;
+  s.xq = g.xq + m0 * (f == kW4A8 ? g.K : g.K / 2);
+  s.xa = g.xa + m0;
+  s.xb = g.xb + m0;
+  s.y = g.y + m0 * g.ldy;
+  s.dbg_acc = g.dbg_acc ? g.dbg_acc + m0 * g.N : nullptr;
+  return s;
+}
+
+// go(part) over the parts of a product whose tiles of bm tokens by bn weight rows fit one grid
+// of `threads` a workgroup: whole tiles of tokens, and where one row of tiles is too wide, weight
+// rows (of one token at a time with raw accumulators).
+template <typename Go>
+hipError_t in_grids(GemmFamily f, const GemmArgs& g, int bm, int bn, int threads, Go&& go) {
+  const int64_t most = max_blocks(threads), tm = (g.M + bm - 1) / bm, tn = (g.N + bn - 1) / bn;
+  if (tm <= most / tn) return go(g);
+  if (tn > most && (g.M == 1 || !g.dbg_acc))
+    return in_parts(g.N, most * bn / 64 * 64, [&](int64_t n, int64_t c) {
+      return in_grids(f, weight_rows(f, g, n, n + c), bm, bn, threads, go);
+    });
+  return in_parts(g.M, tn > most ? 1 : most / tn * bm, [&](int64_t m, int64_t c) {
+    return in_grids(f, token_rows(f, g, m, m + c), bm, bn, threads, go);
+  });
 }
 
 // Kernels of a product: the ring takes weight rows [0, ring_n), the slice kernel the rest.

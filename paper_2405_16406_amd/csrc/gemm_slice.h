@@ -376,12 +376,12 @@ hipError_t launch_slice(const GemmArgs& g, hipStream_t stream) {
   constexpr auto kern = w4_gemm_slice<NB, MB, W, NS, SEG, A8, SW>;
   const hipError_t init = set_max_lds<kern>(S::LDS);
   if (init != hipSuccess) return init;
-  const int64_t tn = SW ? (g.N / 32 + NB / 2 - 1) / (NB / 2) : (g.N + S::BN - 1) / S::BN;
-  const int64_t tm = (g.M + S::BM - 1) / S::BM;
-  if (tn * tm >= (int64_t{1} << 31)) return hipErrorInvalidConfiguration;
-  return launch(kern, dim3(static_cast<unsigned>(tn * tm)), dim3(S::THREADS), S::LDS, stream, g.xq, g.wq,
-                g.M, g.N, static_cast<int>(g.K), static_cast<int>(tm), static_cast<int>(tn * tm),
-                div_magic(static_cast<uint32_t>(tm)), g);
+  return in_grids(F, g, S::BM, S::BN, S::THREADS, [stream](const GemmArgs& p) {
+    const int64_t tn = (p.N + S::BN - 1) / S::BN, tm = (p.M + S::BM - 1) / S::BM;
+    return launch(kern, dim3(static_cast<unsigned>(tn * tm)), dim3(S::THREADS), S::LDS, stream, p.xq, p.wq, p.M, p.N,
+                  static_cast<int>(p.K), static_cast<int>(tm), static_cast<int>(tn * tm),
+                  div_magic(static_cast<uint32_t>(tm)), p);
+  });
 }
 
 // The plan's kernel.  Only the forms slice_ring can ask for are built.

@@ -379,6 +379,9 @@ pack_rows_identity(const uint16_t* x, int64_t ldx, int K, uint8_t* q, float* alp
   }
 }
 
+// Rows of one launch: one workgroup a row, of at most 512 threads in every kernel.
+constexpr int64_t kLaunchRows = max_blocks(512);
+
 hipError_t launch_generic(void (*kern)(RotQuantArgs), const RotQuantArgs& a, hipStream_t stream) {
   const size_t lds = static_cast<size_t>(a.K) * sizeof(float);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -387,9 +390,7 @@ hipError_t launch_generic(void (*kern)(RotQuantArgs), const RotQuantArgs& a, hip
   return launch(kern, dim3(static_cast<unsigned>(a.rows)), dim3(kThreads), static_cast<uint32_t>(lds), stream, a);
 }
 
-}  // namespace
-
-hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
+hipError_t act_rows(const RotQuantArgs& a, hipStream_t stream) {
   if (a.a == 1 && a.b == 1 && a.group == a.K && a.signs == nullptr) {
     // chunks of 8 per thread sized to K, so that the registers (and with them the
     // resident workgroups per CU) follow the row length
@@ -408,7 +409,7 @@ hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
   return launch_generic(had_quant_act_generic, a, stream);
 }
 
-hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream) {
+hipError_t pack_rows(const RotQuantArgs& a, hipStream_t stream) {
   if (a.a == 1 && a.b == 1 && a.signs == nullptr) {
     const dim3 grid(static_cast<unsigned>(a.rows));
     auto go = [&](auto kern, int threads) {
@@ -423,6 +424,16 @@ hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream) {
   const hipError_t e = launch_pack_rows(a, stream);
   if (e != hipErrorNotSupported) return e;
   return launch_generic(pack_w4_generic, a, stream);
+}
+
+}  // namespace
+
+hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream) {
+  return in_parts(a.rows, kLaunchRows, [&](int64_t r, int64_t n) { return act_rows(row_part(a, r, n), stream); });
+}
+
+hipError_t launch_pack_w4(const RotQuantArgs& a, hipStream_t stream) {
+  return in_parts(a.rows, kLaunchRows, [&](int64_t r, int64_t n) { return pack_rows(row_part(a, r, n), stream); });
 }
 
 }  // namespace sq

@@ -595,9 +595,15 @@ hipError_t launch_part(const AttnArgs& a, unsigned parts, hipStream_t stream) {
 
 hipError_t launch_attn_decode_split(const AttnArgs& a, hipStream_t stream) {
   const int64_t NG = (a.H + kAttnGroupHeads - 1) / kAttnGroupHeads;
-  const unsigned parts = static_cast<unsigned>(a.B * a.chunks * NG);
-  if (a.chunks == 1)
-    return a.param16 ? launch_part<true, true>(a, parts, stream) : launch_part<false, true>(a, parts, stream);
+  if (a.chunks == 1) {
+    const int64_t most = max_blocks(64 * kAttnSplitWaves) / NG;
+    return in_parts(a.B, most > 0 ? most : 1, [&](int64_t b, int64_t n) {
+      const AttnArgs s = batch_part(a, b, n);
+      const unsigned blocks = static_cast<unsigned>(n * NG);
+      return a.param16 ? launch_part<true, true>(s, blocks, stream) : launch_part<false, true>(s, blocks, stream);
+    });
+  }
+  const unsigned parts = static_cast<unsigned>(a.B * a.chunks * NG);  // about the CUs
   hipError_t e = a.param16 ? launch_part<true, false>(a, parts, stream) : launch_part<false, false>(a, parts, stream);
   if (e != hipSuccess) return e;
   return launch(attn_decode_combine, dim3(static_cast<unsigned>(a.B * a.H)), dim3(64), 0, stream, a.part, a.out,
@@ -605,9 +611,11 @@ hipError_t launch_attn_decode_split(const AttnArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_attn_decode_kv4(const AttnArgs& a, hipStream_t stream) {
-  const unsigned blocks = static_cast<unsigned>(a.B * a.H);
-  return a.param16 ? launch(attn_decode_kv4<true>, dim3(blocks), dim3(kThreads), 0, stream, a)
-                   : launch(attn_decode_kv4<false>, dim3(blocks), dim3(kThreads), 0, stream, a);
+  const int64_t most = max_blocks(kThreads) / a.H;
+  return in_parts(a.B, most > 0 ? most : 1, [&](int64_t b, int64_t n) {
+    const dim3 blocks(static_cast<unsigned>(n * a.H));
+    return launch(a.param16 ? attn_decode_kv4<true> : attn_decode_kv4<false>, blocks, dim3(kThreads), 0, stream, batch_part(a, b, n));
+  });
 }
 
 }  // namespace sq

@@ -34,6 +34,20 @@ struct RotQuantArgs {
   float* dbg;            // optional fp32 [rows, K]
 };
 
+// The rows [r0, r0 + n) of a launch.
+inline RotQuantArgs row_part(const RotQuantArgs& a, int64_t r0, int64_t n) {
+  RotQuantArgs s = a;
+  const int64_t groups = a.K / a.group;
+  s.rows = n;
+  s.x = a.x + r0 * a.ldx;
+  s.q = a.q + r0 * (a.bits == 8 ? a.K : a.K / 2);
+  s.alpha = a.alpha + r0 * groups;
+  s.beta = a.beta ? a.beta + r0 * groups : nullptr;
+  s.rowsum = a.rowsum ? a.rowsum + r0 : nullptr;
+  s.dbg = a.dbg ? a.dbg + r0 * a.K : nullptr;
+  return s;
+}
+
 // Rotation + asymmetric per-group 4- or 8-bit quantization of activation rows.
 hipError_t launch_had_quant_act(const RotQuantArgs& a, hipStream_t stream);
 // Fast path for K = a*b rows with a registered dense order, per-token groups;
@@ -107,6 +121,23 @@ inline void attn_split(int64_t B, int64_t S, int64_t H, int cus, int64_t& chunks
   if (want < 1) want = 1;
   chunk_batches = (nb + want - 1) / want;
   chunks = (nb + chunk_batches - 1) / chunk_batches;
+}
+
+// The batches [b0, b0 + n) of a call that is not split.
+inline AttnArgs batch_part(const AttnArgs& a, int64_t b0, int64_t n) {
+  AttnArgs s = a;
+  const int64_t heads = b0 * a.H, tokens = heads * a.S, pb = a.param16 ? 2 : 4;
+  const auto param = [&](const void* p) { return static_cast<const void*>(static_cast<const uint8_t*>(p) + tokens * pb); };
+  s.B = n;
+  s.q = a.q + heads * 128;
+  s.kq = a.kq + tokens * 64;
+  s.vq = a.vq + tokens * 64;
+  s.ka = param(a.ka);
+  s.kb = param(a.kb);
+  s.va = param(a.va);
+  s.vb = param(a.vb);
+  s.out = a.out + heads * 128;
+  return s;
 }
 
 hipError_t launch_attn_decode_kv4(const AttnArgs& a, hipStream_t stream);
@@ -200,6 +231,21 @@ inline hipError_t device_cus(int* out) {
   return hipSuccess;
 }
 
+// A grid holds fewer than 2^32 threads.  The runtime does not refuse a larger one but takes the
+// count modulo 2^32 (measured: 2^24 + 1 workgroups of 256 threads ran as one and reported
+// success), so larger work goes out in parts, and launch() refuses what is left.
+constexpr int64_t max_blocks(int threads) { return ((int64_t{1} << 32) - 1) / threads; }
+
+// f(first, count) over [0, n) in parts of at most `most`.
+template <typename F>
+hipError_t in_parts(int64_t n, int64_t most, F&& f) {
+  for (int64_t i = 0; i < n; i += most) {
+    const hipError_t e = f(i, n - i < most ? n - i : most);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Every kernel of the library is launched through here.  What a kernel needs for its first
 // loads are scalar parameters of its own in front of the argument struct, at most 14 dwords:
 // the build has them preloaded into registers, whereas the first scalar load of a struct in
@@ -208,6 +254,7 @@ inline hipError_t device_cus(int* out) {
 // at the start of each kernel).
 template <typename... Params, typename... Args>
 hipError_t launch(void (*kern)(Params...), dim3 grid, dim3 block, uint32_t lds, hipStream_t stream, Args... args) {
+  if (static_cast<int64_t>(grid.x) > max_blocks(static_cast<int>(block.x))) return hipErrorInvalidConfiguration;
   LaunchTiming& t = launch_timing();
   hipExtLaunchKernelGGL(kern, grid, block, lds, stream, t.start, t.stop, 0, args...);
   t.start = nullptr;  // later kernels of the same call only move the stop event

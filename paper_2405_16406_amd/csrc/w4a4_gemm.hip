@@ -557,9 +557,8 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
   constexpr auto kern = w4a4_gemm_ring<WM, WN, TM, TN, NS, WPE, A8>;
   const hipError_t init = set_max_lds<kern>(LDS);
   if (init != hipSuccess) return init;
-  // the 31-bit operand ranges (fits_ring) bound M and N, and with them the tiles, far below 2^31
+  // the 31-bit operand ranges (fits_ring) bound M and N, and with them the tiles, far below a grid
   const int64_t tn = (g.N + R::BN - 1) / R::BN, tm = (g.M + R::BM - 1) / R::BM;
-  if (tn * tm >= (int64_t{1} << 31)) return hipErrorInvalidConfiguration;
   return launch(kern, dim3(static_cast<unsigned>(tn * tm)), dim3(R::THREADS), LDS, stream, g.xq, g.wq, g.M, g.N,
                 static_cast<int>(g.K), static_cast<int>(tm), static_cast<int>(tn * tm),
                 div_magic(static_cast<uint32_t>(tm)), g);
