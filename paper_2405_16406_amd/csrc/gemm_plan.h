@@ -10,10 +10,19 @@ namespace sq {
 
 enum GemmFamily { kW4A4 = 0, kW4A4Swiglu = 1, kW4A8 = 2 };
 
-// A tile of the slice kernel (gemm_slice.h): 16 nb weight rows x 16 mb tokens, K split over
-// `waves` waves, ns ring slots per wave of seg packed bytes per row.
+// How the slice kernel (gemm_slice.h) splits K: over `waves` waves, ns ring slots per wave of seg
+// packed bytes per row.
+struct SliceRing {
+  int waves, ns, seg;
+};
+constexpr bool operator==(const SliceRing& a, const SliceRing& b) {
+  return a.waves == b.waves && a.ns == b.ns && a.seg == b.seg;
+}
+
+// A tile of the slice kernel: 16 nb weight rows x 16 mb tokens.
 struct SlicePlan {
-  int nb, mb, waves, ns, seg;
+  int nb, mb;
+  SliceRing ring;
   float us;  // its estimated time
 };
 
@@ -52,28 +61,30 @@ constexpr bool slice_has(GemmFamily f, int nb, int mb) {
 //          6 x 3 .95 | .94 | .95 | .94 | 1.01        4 x 4 1.00 | 1.04 | 1.02 | 1.01 | 1.01
 // ([300 x 11008] x [4096 x 11008] 4 x 5: 19.4 to 17.8 us; [24 x 4096] x [4096 x 4096] 2 x 1: 4.1
 // to 3.5.)
-inline bool slice_eight_waves(GemmFamily f, int nb, int mb, int64_t K) {
-  if (f == kW4A4Swiglu || K >= 16384) return false;
+constexpr bool slice_eight_waves(GemmFamily f, int nb, int mb, int64_t K) {
+  if (f == kW4A4Swiglu || (K >= 16384 && !(f == kW4A4 && nb * mb >= 32))) return false;
   return K < 8192 || (nb * mb >= 12 && !(f == kW4A8 && nb == 4 && mb == 4));
 }
-inline void slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, int* waves, int* ns, int* seg) {
+constexpr SliceRing slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round) {
   const bool a8 = f == kW4A8;
-  *waves = 4;
-  if (one_round && slice_eight_waves(f, nb, mb, K)) {
-    *waves = 8;
-    *ns = 1;
-    *seg = 64;
-  } else if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) {
-    *ns = K >= 8192 ? 2 : 1;
-    *seg = 128;
-  } else if (one_round) {
-    *ns = 2;
-    *seg = (a8 ? nb + mb <= 4 && K >= 8192
-               : (nb + mb <= 5 && K >= 8192) || (nb + mb <= 9 && K >= 16384)) ? 128 : 64;
-  } else {
-    *ns = 1;
-    *seg = (nb + mb <= (a8 ? 5 : 8) && K > 4096) || (!a8 && nb + mb <= 9 && K >= 16384) ? 128 : 64;
-  }
+  if (one_round && slice_eight_waves(f, nb, mb, K)) return {8, 1, 64};
+  if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) return {4, K >= 8192 ? 2 : 1, 128};
+  if (one_round)
+    return {4, 2, (a8 ? nb + mb <= 4 && K >= 8192
+                      : (nb + mb <= 5 && K >= 8192) || (nb + mb <= 9 && K >= 16384)) ? 128 : 64};
+  return {4, 1, (nb + mb <= (a8 ? 5 : 8) && K > 4096) || (!a8 && nb + mb <= 9 && K >= 16384) ? 128 : 64};
+}
+
+// The rings a shape is built with: those slice_ring returns for it (one K of each range the rule
+// tells apart).
+constexpr SliceRing kSliceRing[] = {{8, 1, 64}, {4, 2, 128}, {4, 1, 128}, {4, 2, 64}, {4, 1, 64}};
+constexpr int kSliceRings = sizeof(kSliceRing) / sizeof(kSliceRing[0]);
+constexpr bool slice_built(GemmFamily f, int nb, int mb, const SliceRing& r) {
+  constexpr int64_t kRanges[] = {4096, 4160, 8192, 16384};
+  if (!slice_has(f, nb, mb)) return false;
+  for (int64_t K : kRanges)
+    if (slice_ring(f, nb, mb, K, false) == r || slice_ring(f, nb, mb, K, true) == r) return true;
+  return false;
 }
 
 // Estimated times (us), fitted to 850 measured products of M = 1 .. 3600 tokens against
@@ -111,7 +122,7 @@ inline double slice_us(GemmFamily f, const GemmArgs& g, int shape, int cus) {
 }
 
 inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
-  SlicePlan best{0, 0, 0, 0, 0, 0.0f};
+  SlicePlan best{0, 0, {}, 0.0f};
   double us = 0.0;
   for (int s = 0; s < kSliceShapes; ++s) {
     const int nb = kSliceShape[s][0], mb = kSliceShape[s][1];
@@ -125,7 +136,7 @@ inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
   }
   best.us = static_cast<float>(us);
   const int64_t tiles = ((g.M + 16 * best.mb - 1) / (16 * best.mb)) * ((g.N + 16 * best.nb - 1) / (16 * best.nb));
-  slice_ring(f, best.nb, best.mb, g.K, tiles <= cus, &best.waves, &best.ns, &best.seg);
+  best.ring = slice_ring(f, best.nb, best.mb, g.K, tiles <= cus);
   return best;
 }
 
@@ -140,6 +151,12 @@ constexpr RingTile ring_tile(GemmFamily f, bool large) {
 inline int64_t ring_tiles(GemmFamily f, const GemmArgs& g, bool large) {
   const RingTile t = ring_tile(f, large);
   return ((g.M + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn);
+}
+// The ring's 32-bit operand offsets, rows past the tiles' ends included, fit 31 bits.
+inline bool ring_fits(GemmFamily f, const GemmArgs& g, bool large) {
+  const RingTile t = ring_tile(f, large);
+  const int64_t kb = g.K / 2, ka = f == kW4A8 ? g.K : kb;
+  return (g.M + t.bm) * ka + 128 < (int64_t{1} << 31) && (g.N + t.bn) * kb + 64 < (int64_t{1} << 31);
 }
 // At least as many 256 x 256 tiles as a 256-CU part has CUs.
 inline bool ring_large(GemmFamily f, const GemmArgs& g) { return ring_tiles(f, g, true) >= 256; }
@@ -205,19 +222,18 @@ struct GemmPlan {
 // The slice kernel alone, the ring alone, or the ring on as many weight rows as fill whole
 // rounds of its tiles and the slice kernel on the rest, where the last round would leave CUs
 // idle; the ring wherever the others are not at least 7 % faster by the estimates, which is
-// about their error (fits(sub, large): the ring's 31-bit offsets cover the product).
+// about their error.
 // Measured on MI355X (us, against the ring alone): W4A8 [1024 x 22016 x 4096] 104 vs 117 (256
 // tiles and 5632 rows of slices instead of two rounds for 344 tiles), [1536 x 22016 x 4096]
 // 138 vs 181, [1100 x 8192 x 28672] 306 vs 446; W4A4 [2300 x 4096 x 14336] 125 vs 176, [2100 x
 // 8192 x 8192] 120 vs 168; with SiLU [1300 x 22016 x 4096] 106 vs 140.
-template <typename Fits>
-GemmPlan plan_gemm(GemmFamily f, const GemmArgs& g, int cus, Fits&& fits) {
+inline GemmPlan plan_gemm(GemmFamily f, const GemmArgs& g, int cus) {
   constexpr double kClear = 0.93;
   GemmPlan best{0, false, plan_slice(f, g, cus)};
   if (g.M <= 16) return best;
   double us = best.slice.us;
   const bool whole = ring_large(f, g);
-  if (fits(g, whole)) {
+  if (ring_fits(f, g, whole)) {
     const double t = ring_us(f, g, whole, ring_tiles(f, g, whole), cus);
     if (kClear * t <= us) {
       best = GemmPlan{g.N, whole, SlicePlan{}};
@@ -231,7 +247,7 @@ GemmPlan plan_gemm(GemmFamily f, const GemmArgs& g, int cus, Fits&& fits) {
     const int64_t n1 = rounds * cus / tm * t.bn;
     if (n1 <= 0 || n1 >= g.N) continue;
     const GemmArgs head = weight_rows(f, g, 0, n1), tail = weight_rows(f, g, n1, g.N);
-    if (!fits(head, large)) continue;
+    if (!ring_fits(f, head, large)) continue;
     const SlicePlan p = plan_slice(f, tail, cus);
     const double u = ring_us(f, head, large, tm * (n1 / t.bn), cus) + p.us;
     if (u < kClear * us) {

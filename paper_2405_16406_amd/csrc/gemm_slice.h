@@ -384,26 +384,16 @@ hipError_t launch_slice(const GemmArgs& g, hipStream_t stream) {
   });
 }
 
-// The plan's kernel.  Only the forms slice_ring can ask for are built.
+// The plan's kernel, of those slice_ring can ask for.
 template <GemmFamily F>
 hipError_t launch_slice_plan(const GemmArgs& g, const SlicePlan& p, hipStream_t stream) {
   hipError_t e = hipErrorInvalidValue;
-  static_for<kSliceShapes>([&](auto sc) {
-    constexpr int nb = kSliceShape[decltype(sc)::value][0], mb = kSliceShape[decltype(sc)::value][1];
-    if constexpr (slice_has(F, nb, mb)) {
-      if (p.nb != nb || p.mb != mb) return;
-      constexpr bool a8 = F == kW4A8;
-      if (p.waves == 8) {
-        if constexpr (F != kW4A4Swiglu) e = launch_slice<nb, mb, 8, 1, 64, F>(g, stream);
-      } else if (p.seg == 128) {
-        if constexpr (nb + mb <= (a8 ? 4 : 9))
-          if (p.ns == 2) e = launch_slice<nb, mb, 4, 2, 128, F>(g, stream);
-        if constexpr (nb + mb <= (a8 ? 5 : 9))
-          if (p.ns == 1) e = launch_slice<nb, mb, 4, 1, 128, F>(g, stream);
-      } else {
-        e = p.ns == 2 ? launch_slice<nb, mb, 4, 2, 64, F>(g, stream) : launch_slice<nb, mb, 4, 1, 64, F>(g, stream);
-      }
-    }
+  static_for<kSliceShapes * kSliceRings>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr int nb = kSliceShape[i / kSliceRings][0], mb = kSliceShape[i / kSliceRings][1];
+    constexpr SliceRing r = kSliceRing[i % kSliceRings];
+    if constexpr (slice_built(F, nb, mb, r))
+      if (p.nb == nb && p.mb == mb && p.ring == r) e = launch_slice<nb, mb, r.waves, r.ns, r.seg, F>(g, stream);
   });
   return e;
 }

@@ -541,23 +541,18 @@ w4a4_gemm_ring(const uint8_t* xq, const uint8_t* wq, int64_t M, int64_t N, int K
   }
 }
 
-template <int WM, int WN, int TM, int TN, int NS, bool A8 = false>
-bool fits_ring(const GemmArgs& g) {
-  using R = Ring<WM, WN, TM, TN, NS, A8>;
-  const int64_t kb = g.K / 2, ka = A8 ? g.K : kb;
-  return (g.M + R::BM) * ka + 128 < (int64_t{1} << 31) && (g.N + R::BN) * kb + 64 < (int64_t{1} << 31);
-}
-
 // WPE: waves per SIMD the registers must allow (2 for two 4-wave workgroups per CU).
-template <int WM, int WN, int TM, int TN, int NS, int WPE = 1, bool A8 = false>
+template <GemmFamily F, bool LARGE, int WM, int WN, int TM, int TN, int NS, int WPE = 1>
 hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
+  constexpr bool A8 = F == kW4A8;
   using R = Ring<WM, WN, TM, TN, NS, A8>;
+  static_assert(R::BM == ring_tile(F, LARGE).bm && R::BN == ring_tile(F, LARGE).bn, "the tile the plan counts with");
   constexpr int LDS = RingLds<WM, WN, TM, TN, NS, A8>::BYTES;
   static_assert(LDS <= 160 * 1024, "LDS of one CU");
   constexpr auto kern = w4a4_gemm_ring<WM, WN, TM, TN, NS, WPE, A8>;
   const hipError_t init = set_max_lds<kern>(LDS);
   if (init != hipSuccess) return init;
-  // the 31-bit operand ranges (fits_ring) bound M and N, and with them the tiles, far below a grid
+  // the 31-bit operand ranges (ring_fits) bound M and N, and with them the tiles, far below a grid
   const int64_t tn = (g.N + R::BN - 1) / R::BN, tm = (g.M + R::BM - 1) / R::BM;
   return launch(kern, dim3(static_cast<unsigned>(tn * tm)), dim3(R::THREADS), LDS, stream, g.xq, g.wq, g.M, g.N,
                 static_cast<int>(g.K), static_cast<int>(tm), static_cast<int>(tn * tm),
@@ -577,7 +572,7 @@ bool swiglu_covered(const GemmArgs& g, int cus) {
     return (g.N + past) * kb + 64 < lim;
   }
   if (g.M <= 128) return (g.M + 128) * kb + 128 < lim && (g.N + 128) * kb + 64 < lim;
-  return ring_large(kW4A4Swiglu, g) ? fits_ring<2, 4, 4, 2, 4>(g) : fits_ring<2, 2, 4, 2, 3>(g);
+  return ring_fits(kW4A4Swiglu, g, ring_large(kW4A4Swiglu, g));
 }
 
 // Ring tiles.  At least as many 256 x 256 tiles as CUs -> those: 8 waves of 128 x 64 and four
@@ -590,14 +585,11 @@ bool swiglu_covered(const GemmArgs& g, int cus) {
 // and with fewer than 256 large tiles the half ones: 4-bit [2048 x 4096 x 11008] 83.5 vs 123,
 // 8-bit 104 vs 150.
 hipError_t launch_ring_tiles(GemmFamily f, const GemmArgs& g, bool large, hipStream_t stream) {
-  if (f == kW4A8) return large ? launch_ring<4, 2, 2, 4, 3, 1, true>(g, stream) : launch_ring<2, 4, 2, 2, 4, 1, true>(g, stream);
-  if (large) return launch_ring<2, 4, 4, 2, 4>(g, stream);
-  return f == kW4A4Swiglu ? launch_ring<2, 2, 4, 2, 3, 2>(g, stream) : launch_ring<2, 4, 2, 2, 3>(g, stream);
-}
-bool fits_ring_tiles(GemmFamily f, const GemmArgs& g, bool large) {
-  if (f == kW4A8) return large ? fits_ring<4, 2, 2, 4, 3, true>(g) : fits_ring<2, 4, 2, 2, 4, true>(g);
-  if (large) return fits_ring<2, 4, 4, 2, 4>(g);
-  return f == kW4A4Swiglu ? fits_ring<2, 2, 4, 2, 3>(g) : fits_ring<2, 4, 2, 2, 3>(g);
+  if (f == kW4A8)
+    return large ? launch_ring<kW4A8, true, 4, 2, 2, 4, 3>(g, stream) : launch_ring<kW4A8, false, 2, 4, 2, 2, 4>(g, stream);
+  if (large) return launch_ring<kW4A4, true, 2, 4, 4, 2, 4>(g, stream);
+  return f == kW4A4Swiglu ? launch_ring<kW4A4Swiglu, false, 2, 2, 4, 2, 3, 2>(g, stream)
+                          : launch_ring<kW4A4, false, 2, 4, 2, 2, 3>(g, stream);
 }
 
 }  // namespace
@@ -608,7 +600,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream) {
   const hipError_t e = device_cus(&cus);
   if (e != hipSuccess) return e;
   if (f == kW4A4Swiglu && !swiglu_covered(g, cus)) return hipErrorNotSupported;
-  const GemmPlan p = plan_gemm(f, g, cus, [f](const GemmArgs& s, bool large) { return fits_ring_tiles(f, s, large); });
+  const GemmPlan p = plan_gemm(f, g, cus);
   if (p.ring_n > 0) {
     const hipError_t r = launch_ring_tiles(f, p.ring_n < g.N ? weight_rows(f, g, 0, p.ring_n) : g, p.large, stream);
     if (r != hipSuccess || p.ring_n == g.N) return r;

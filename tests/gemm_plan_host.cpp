@@ -33,3 +33,26 @@ extern "C" int grids(int f, int64_t M, int64_t N, int64_t K, int64_t ldy, int db
   });
   return e == hipSuccess ? n : -1;
 }
+
+// The plan of a product: ring_n, large, and the slice kernel's nb, mb, waves, ns, seg (zeros without it).
+extern "C" void plan(int f, int64_t M, int64_t N, int64_t K, int dbg, int cus, int* out) {
+  sq::GemmArgs g{};
+  g.M = M, g.N = N, g.K = K, g.a8 = f == sq::kW4A8, g.swiglu = f == sq::kW4A4Swiglu;
+  g.dbg_acc = dbg ? at<int32_t>(64) : nullptr;
+  const sq::GemmPlan p = sq::plan_gemm(static_cast<sq::GemmFamily>(f), g, cus);
+  const int v[7] = {static_cast<int>(p.ring_n), p.large, p.slice.nb, p.slice.mb, p.slice.ring.waves, p.slice.ring.ns, p.slice.ring.seg};
+  for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
+
+// The slice kernels a family is built with (nb, mb, waves, ns, seg each); returns their count.
+extern "C" int built(int f, int* out) {
+  int n = 0;
+  for (const auto& s : sq::kSliceShape)
+    for (const sq::SliceRing& r : sq::kSliceRing)
+      if (sq::slice_built(static_cast<sq::GemmFamily>(f), s[0], s[1], r)) {
+        const int v[5] = {s[0], s[1], r.waves, r.ns, r.seg};
+        for (int i = 0; i < 5; ++i) out[5 * n + i] = v[i];
+        ++n;
+      }
+  return n;
+}

@@ -2,11 +2,14 @@
 
 import ctypes
 import os
+import random
 import subprocess
 
 import pytest
 
 from paper_2405_16406_amd import build
+
+import test_gpu_slice
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 W4A4, SWIGLU, W4A8 = range(3)
@@ -19,6 +22,58 @@ def plan(tmp_path_factory):
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return ctypes.CDLL(out)
+
+
+def plan_of(lib, family, M, N, K, dbg, cus=256):
+    """(weight rows of the ring kernel, its large tiles, the slice kernel's nb, mb, waves, ns, seg)"""
+    out = (ctypes.c_int * 7)()
+    lib.plan(family, ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), dbg, cus, out)
+    return tuple(out)
+
+
+def built(lib, family):
+    out = (ctypes.c_int * 1024)()
+    return {tuple(out[5 * i:5 * i + 5]) for i in range(lib.built(family, out))}
+
+
+def listed(family):
+    """Sizes of tests/test_gpu_slice.py that run against the oracle."""
+    t = test_gpu_slice
+    name = ("w4a4", "swiglu", "w4a8")[family]
+    own = {W4A4: t.W4A4, SWIGLU: [c[:3] for c in t.SWIGLU], W4A8: t.W4A8}[family]
+    split = t.SPLIT_SWIGLU if family == SWIGLU else [c[:3] for c in t.SPLIT if c[3] == (family == W4A8)]
+    sizes = own + [c[:3] for c in t.FORMS if c[3] == name] + split
+    return [(M, 2 * N if family == SWIGLU else N, K) for M, N, K in sizes]
+
+
+@pytest.mark.parametrize("family", [W4A4, SWIGLU, W4A8])
+def test_every_slice_kernel_is_tested(plan, family):
+    """Each kernel that is built is the plan of a listed size (on 256 CUs), and every plan is built."""
+    plans = [plan_of(plan, family, *c, dbg) for c in listed(family) for dbg in ((0,) if family == SWIGLU else (0, 1))]
+    reached = {p[2:] for p in plans if p[2]}
+    assert reached == built(plan, family)
+
+
+def test_split_sizes_are_split(plan):
+    t = test_gpu_slice
+    for M, N, K, a8 in t.SPLIT:
+        assert 0 < plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 0)[0] < N, (M, N, K)
+        assert plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 1)[0] in (0, N), (M, N, K)
+    for M, I, K in t.SPLIT_SWIGLU:
+        assert 0 < plan_of(plan, SWIGLU, M, 2 * I, K, 0)[0] < 2 * I, (M, I, K)
+
+
+@pytest.mark.parametrize("family", [W4A4, SWIGLU, W4A8])
+def test_every_plan_is_built(plan, family):
+    """The tile and ring of any product are among the built kernels, on parts of other sizes too."""
+    rng, forms = random.Random(family), built(plan, family)
+    for _ in range(20000):
+        M, N = (int(2 ** rng.uniform(0, top)) for top in (13, 17))
+        K = 64 * int(2 ** rng.uniform(0, 11 if family == W4A8 else 14))
+        if family == SWIGLU:
+            N = max(64, N // 64 * 64)
+        p = plan_of(plan, family, M, N, K, rng.randrange(2) if family != SWIGLU else 0, rng.choice([256, 256, 304, 128, 8, 1]))
+        assert 0 <= p[0] <= N and (p[0] == N or p[2:] in forms), (M, N, K, p)
 
 
 # Products of more workgroups than one grid holds (2^32 threads), and their neighbours that fit.

@@ -59,13 +59,15 @@ def test_w4a8_slice(M, N, K):
 
 # The other tiles, wave counts, ring depths and segment lengths of the three families: four waves
 # in several rounds and over a long K, eight waves elsewhere ("swiglu": rows of gate alone).
+# tests/test_gemm_plan.py checks that the lists of this file reach every kernel that is built.
 FORMS = [(2828, 33, 8640, "w4a4"), (98, 2952, 9536, "w4a4"), (107, 6031, 17344, "w4a4"), (169, 7901, 17216, "w4a4"),
       (1640, 1810, 192, "w4a4"), (3681, 386, 192, "w4a4"), (1, 4480, 1344, "swiglu"), (17, 4256, 1344, "swiglu"),
       (33, 4352, 2112, "swiglu"), (33, 2208, 192, "swiglu"), (1, 8352, 448, "swiglu"), (49, 3072, 16704, "swiglu"),
       (37, 8384, 576, "swiglu"), (402, 2336, 192, "swiglu"), (97, 3488, 17472, "swiglu"), (49, 4512, 192, "swiglu"),
       (92, 4192, 192, "swiglu"), (3663, 544, 192, "swiglu"), (3269, 288, 192, "swiglu"), (1, 4451, 2880, "w4a8"),
       (19, 9492, 3136, "w4a8"), (17, 6603, 8640, "w4a8"), (34, 6421, 8384, "w4a8"), (51, 9699, 8256, "w4a8"),
-      (65, 12375, 192, "w4a8")]
+      (65, 12375, 192, "w4a8"), (641, 2946, 64, "w4a4"), (875, 608, 16512, "swiglu"), (558, 906, 17024, "w4a8"),
+      (1822, 828, 17728, "w4a8"), (845, 1233, 16448, "w4a8"), (875, 1265, 16512, "w4a8"), (1390, 1246, 16640, "w4a8")]
 
 
 @pytest.mark.parametrize("M,N,K,family", FORMS)
@@ -77,16 +79,19 @@ def test_slice_forms(M, N, K, family):
 
 # Products that fill whole rounds of ring tiles and leave a rest for the slice kernel.  The
 # accumulators' call runs as one kernel, so its outputs check the split one's bit for bit.
-@pytest.mark.parametrize("M,N,K,a8", [(520, 22010, 576, False), (1000, 16448, 1088, False), (2100, 8200, 1088, False),
-                                      (1300, 12288, 1088, False), (1000, 16448, 576, True), (2100, 8200, 576, True),
-                                      (2100, 22010, 1088, True)])
+SPLIT = [(520, 22010, 576, False), (1000, 16448, 1088, False), (2100, 8200, 1088, False), (1300, 12288, 1088, False),
+         (1000, 16448, 576, True), (2100, 8200, 576, True), (2100, 22010, 1088, True)]
+SPLIT_SWIGLU = [(1000, 8224, 1088), (2100, 4128, 1088), (2600, 6144, 1088)]
+
+
+@pytest.mark.parametrize("M,N,K,a8", SPLIT)
 def test_ring_and_slice(M, N, K, a8):
     say(f"ring and slice on parts of one product M={M} N={N} K={K} 8-bit={a8}")
     rows = np.array([0, 1, M // 2, M - 1])
     (gemm8_case if a8 else gemm_case)(M, N, K, seed=M + N, sample_rows=rows)
 
 
-@pytest.mark.parametrize("M,I,K", [(1000, 8224, 1088), (2100, 4128, 1088), (2600, 6144, 1088)])
+@pytest.mark.parametrize("M,I,K", SPLIT_SWIGLU)
 def test_ring_and_slice_swiglu(M, I, K):
     say(f"ring and slice on parts of one gate/up product M={M} I={I} K={K}")
     swiglu_case(M, I, K, seed=M + I, sample_rows=np.arange(0, M, 97))
