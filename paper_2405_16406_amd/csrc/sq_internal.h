@@ -192,22 +192,6 @@ hipError_t set_max_lds(int bytes) {
   return e;
 }
 
-// Workgroups of kernel Kern (threads, dynamic LDS bytes) that fit one CU, queried once per
-// process (after set_max_lds); a failed query is not remembered.
-template <auto Kern>
-hipError_t blocks_per_cu(int threads, int lds, int* out) {
-  static std::atomic<int> cached{0};
-  int v = cached.load(std::memory_order_acquire);
-  if (v == 0) {
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, Kern, threads, lds);
-    if (e != hipSuccess) return e;
-    if (v < 1) v = 1;
-    cached.store(v, std::memory_order_release);
-  }
-  *out = v;
-  return hipSuccess;
-}
-
 // Compute units of the current device (queried per device and cached; a failed query is
 // not remembered).
 inline hipError_t device_cus(int* out) {
