@@ -93,6 +93,14 @@ constexpr bool slice_built(GemmFamily f, int nb, int mb, const SliceRing& r) {
 // more), next to the time the operands take from memory and from the L2s.  The tile chosen is
 // 1 - 2.5 % off the best measured one on average; from 300 tokens the estimate is 5 - 7 % off
 // (rms), which is why the ring below is left only for a clear gain.
+// K < 4096 lies outside that fit: there the sums and stores of a tile's blocks (kBlockUs each) and
+// the ring's start (kRingStartUs) are no longer hidden in the rest.  With the two terms, on 756
+// products of K = 64 .. 4032 (weights not in a cache), the time is 1.6 % lower on average and 11
+// instead of 29 are more than 8 % slower than on the kernels before this one: SiLU [1500 x 4096 x
+// 256] 16.4 on slices, 12.2 on the ring; 8-bit [300 x 32768 x 256] 27.2 and 17.2; 4-bit [3000 x 2048
+// x 2048] 25.4 and 23.0; [16 x 65536 x 128] 11.1 on 8 x 4 tiles, 8.0 on 4 x 2.
+constexpr double kBlockUs = 0.05, kRingStartUs = 3.0;
+constexpr bool short_k(const GemmArgs& g) { return g.K < 4096; }
 struct SliceCost {
   float base, mem_tb, tile, ceil, alone, l2_tb;
   float shape[kSliceShapes];  // us per 128 k of a round, in the order of kSliceShape
@@ -109,7 +117,8 @@ inline double slice_us(GemmFamily f, const GemmArgs& g, int shape, int cus) {
   const int nb = kSliceShape[shape][0], mb = kSliceShape[shape][1], abytes = f == kW4A8 ? 2 : 1;
   const double M = static_cast<double>(g.M), N = static_cast<double>(g.N), K = static_cast<double>(g.K);
   const double tiles = std::ceil(M / (16 * mb)) * std::ceil(N / (16 * nb)), rounds = tiles / cus;
-  double comp = (c.ceil * std::ceil(rounds) + (1 - c.ceil) * rounds) * (c.tile + K / 128 * c.shape[shape]);
+  double comp = (c.ceil * std::ceil(rounds) + (1 - c.ceil) * rounds) *
+                (c.tile + K / 128 * c.shape[shape] + (short_k(g) ? kBlockUs * nb * mb : 0.0));
   if (rounds <= 1) comp *= c.alone;
   double mem = (N * K / 2 + M * K * abytes / 2 + (f == kW4A4Swiglu ? M * N : 2 * M * N)) / c.mem_tb * 1e-6;
   if (rounds < 1) mem /= std::sqrt(rounds);  // idle CUs stream nothing
@@ -168,7 +177,7 @@ inline double ring_us(GemmFamily f, const GemmArgs& g, bool large, int64_t tiles
                                      {{4.81, 0.8457, 0.3277}, {7.34, 1.3151, 0.5921}}};
   const double k = static_cast<double>(g.K) / 128, rounds = static_cast<double>(tiles) / cus;
   const double* c = kCost[f][large];
-  return c[0] + k * (c[1] * std::ceil(rounds) + c[2] * rounds);
+  return c[0] + k * (c[1] * std::ceil(rounds) + c[2] * rounds) + (short_k(g) ? kRingStartUs : 0.0);
 }
 
 // The weight rows [r0, r1) of a product.

@@ -61,6 +61,10 @@ def test_split_sizes_are_split(plan):
         assert plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 1)[0] in (0, N), (M, N, K)
     for M, I, K in t.SPLIT_SWIGLU:
         assert 0 < plan_of(plan, SWIGLU, M, 2 * I, K, 0)[0] < 2 * I, (M, I, K)
+    for M, N, K, a8 in t.WHOLE:
+        assert plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 0)[0] == N, (M, N, K)
+    for M, I, K in t.WHOLE_SWIGLU:
+        assert plan_of(plan, SWIGLU, M, 2 * I, K, 0)[0] == 2 * I, (M, I, K)
 
 
 @pytest.mark.parametrize("family", [W4A4, SWIGLU, W4A8])
@@ -113,3 +117,14 @@ def check_parts(plan, family, M, N, K, bm, bn, threads, dbg):
     assert area == M * N and len({s[:2] for s in seen}) == n
     if -(-M // bm) * -(-N // bn) * threads < 1 << 32:
         assert n == 1
+
+
+# Products of a short K, where stores and the ring's start outweigh what the estimates are fitted
+# to: measured, the ring's tiles (all N) or small slices (few blocks a tile) are the faster ones.
+@pytest.mark.parametrize("family,M,N,K,ring", [(SWIGLU, 1500, 4096, 256, True), (W4A8, 128, 65536, 128, True),
+                                               (W4A8, 300, 32768, 256, True), (W4A4, 3000, 2048, 2048, True),
+                                               (W4A4, 24, 32768, 128, False), (SWIGLU, 10, 36864, 64, False),
+                                               (W4A4, 11, 29897, 64, False), (W4A8, 22, 25762, 128, False)])
+def test_short_k(plan, family, M, N, K, ring):
+    p = plan_of(plan, family, M, N, K, 0)
+    assert p[0] == N if ring else p[0] == 0 and p[2] * p[3] <= 8, p

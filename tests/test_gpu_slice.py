@@ -67,7 +67,9 @@ FORMS = [(2828, 33, 8640, "w4a4"), (98, 2952, 9536, "w4a4"), (107, 6031, 17344, 
       (92, 4192, 192, "swiglu"), (3663, 544, 192, "swiglu"), (3269, 288, 192, "swiglu"), (1, 4451, 2880, "w4a8"),
       (19, 9492, 3136, "w4a8"), (17, 6603, 8640, "w4a8"), (34, 6421, 8384, "w4a8"), (51, 9699, 8256, "w4a8"),
       (65, 12375, 192, "w4a8"), (641, 2946, 64, "w4a4"), (875, 608, 16512, "swiglu"), (558, 906, 17024, "w4a8"),
-      (1822, 828, 17728, "w4a8"), (845, 1233, 16448, "w4a8"), (875, 1265, 16512, "w4a8"), (1390, 1246, 16640, "w4a8")]
+      (1822, 828, 17728, "w4a8"), (845, 1233, 16448, "w4a8"), (875, 1265, 16512, "w4a8"), (1390, 1246, 16640, "w4a8"),
+      (82, 8316, 64, "w4a4"), (1986, 1554, 128, "w4a4"), (403, 160, 64, "swiglu"), (167, 2752, 64, "swiglu"),
+      (880, 864, 64, "swiglu")]
 
 
 @pytest.mark.parametrize("M,N,K,family", FORMS)
@@ -80,18 +82,21 @@ def test_slice_forms(M, N, K, family):
 # Products that fill whole rounds of ring tiles and leave a rest for the slice kernel.  The
 # accumulators' call runs as one kernel, so its outputs check the split one's bit for bit.
 SPLIT = [(520, 22010, 576, False), (1000, 16448, 1088, False), (2100, 8200, 1088, False), (1300, 12288, 1088, False),
-         (1000, 16448, 576, True), (2100, 8200, 576, True), (2100, 22010, 1088, True)]
-SPLIT_SWIGLU = [(1000, 8224, 1088), (2100, 4128, 1088), (2600, 6144, 1088)]
+         (1000, 16448, 576, True), (2479, 3437, 1152, True), (2100, 22010, 1088, True)]
+SPLIT_SWIGLU = [(1000, 8224, 1088), (2377, 1728, 1600), (2697, 1568, 1408)]
+# ... and such that the ring takes whole, its last round short
+WHOLE = [(2100, 8200, 576, True)]
+WHOLE_SWIGLU = [(2100, 4128, 1088), (2600, 6144, 1088)]
 
 
-@pytest.mark.parametrize("M,N,K,a8", SPLIT)
+@pytest.mark.parametrize("M,N,K,a8", SPLIT + WHOLE)
 def test_ring_and_slice(M, N, K, a8):
     say(f"ring and slice on parts of one product M={M} N={N} K={K} 8-bit={a8}")
     rows = np.array([0, 1, M // 2, M - 1])
     (gemm8_case if a8 else gemm_case)(M, N, K, seed=M + N, sample_rows=rows)
 
 
-@pytest.mark.parametrize("M,I,K", SPLIT_SWIGLU)
+@pytest.mark.parametrize("M,I,K", SPLIT_SWIGLU + WHOLE_SWIGLU)
 def test_ring_and_slice_swiglu(M, I, K):
     say(f"ring and slice on parts of one gate/up product M={M} I={I} K={K}")
     swiglu_case(M, I, K, seed=M + I, sample_rows=np.arange(0, M, 97))
