@@ -65,8 +65,14 @@ constexpr bool slice_eight_waves(GemmFamily f, int nb, int mb, int64_t K) {
   if (f == kW4A4Swiglu || (K >= 16384 && !(f == kW4A4 && nb * mb >= 32))) return false;
   return K < 8192 || (nb * mb >= 12 && !(f == kW4A8 && nb == 4 && mb == 4));
 }
-constexpr SliceRing slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round) {
+// One-block tiles over a long K on few of the CUs (half; a quarter with 8-bit codes): eight waves
+// with two long slots, since what bounds them is the bytes a CU has in flight (us, M = 1, four
+// waves | eight; weights not in a cache): [1024 x 14336] 9.6 | 8.0, [64 x 32768] 13.4 | 9.4, [2048 x
+// 28672] 16.7 | 14.2, 8-bit [1024 x 28672] 17.0 | 15.1; 8-bit on half of the CUs [16 x 14336] x [2048
+// x 14336] 10.2 | 12.3, and with a tile for every CU they are even.
+constexpr SliceRing slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one_round, bool few) {
   const bool a8 = f == kW4A8;
+  if (few && nb == 1 && mb == 1 && K >= 8192) return {8, 2, 128};
   if (one_round && slice_eight_waves(f, nb, mb, K)) return {8, 1, 64};
   if (mb == 1 && (nb == 1 || (nb == 2 && K >= 8192))) return {4, K >= 8192 ? 2 : 1, 128};
   if (one_round)
@@ -77,13 +83,14 @@ constexpr SliceRing slice_ring(GemmFamily f, int nb, int mb, int64_t K, bool one
 
 // The rings a shape is built with: those slice_ring returns for it (one K of each range the rule
 // tells apart).
-constexpr SliceRing kSliceRing[] = {{8, 1, 64}, {4, 2, 128}, {4, 1, 128}, {4, 2, 64}, {4, 1, 64}};
+constexpr SliceRing kSliceRing[] = {{8, 2, 128}, {8, 1, 64}, {4, 2, 128}, {4, 1, 128}, {4, 2, 64}, {4, 1, 64}};
 constexpr int kSliceRings = sizeof(kSliceRing) / sizeof(kSliceRing[0]);
 constexpr bool slice_built(GemmFamily f, int nb, int mb, const SliceRing& r) {
   constexpr int64_t kRanges[] = {4096, 4160, 8192, 16384};
   if (!slice_has(f, nb, mb)) return false;
   for (int64_t K : kRanges)
-    if (slice_ring(f, nb, mb, K, false) == r || slice_ring(f, nb, mb, K, true) == r) return true;
+    for (int rounds = 0; rounds < 3; ++rounds)
+      if (slice_ring(f, nb, mb, K, rounds > 0, rounds > 1) == r) return true;
   return false;
 }
 
@@ -145,7 +152,7 @@ inline SlicePlan plan_slice(GemmFamily f, const GemmArgs& g, int cus) {
   }
   best.us = static_cast<float>(us);
   const int64_t tiles = ((g.M + 16 * best.mb - 1) / (16 * best.mb)) * ((g.N + 16 * best.nb - 1) / (16 * best.nb));
-  best.ring = slice_ring(f, best.nb, best.mb, g.K, tiles <= cus);
+  best.ring = slice_ring(f, best.nb, best.mb, g.K, tiles <= cus, (f == kW4A8 ? 4 : 2) * tiles <= cus);
   return best;
 }
 

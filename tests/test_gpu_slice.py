@@ -69,7 +69,8 @@ FORMS = [(2828, 33, 8640, "w4a4"), (98, 2952, 9536, "w4a4"), (107, 6031, 17344, 
       (65, 12375, 192, "w4a8"), (641, 2946, 64, "w4a4"), (875, 608, 16512, "swiglu"), (558, 906, 17024, "w4a8"),
       (1822, 828, 17728, "w4a8"), (845, 1233, 16448, "w4a8"), (875, 1265, 16512, "w4a8"), (1390, 1246, 16640, "w4a8"),
       (82, 8316, 64, "w4a4"), (1986, 1554, 128, "w4a4"), (403, 160, 64, "swiglu"), (167, 2752, 64, "swiglu"),
-      (880, 864, 64, "swiglu")]
+      (880, 864, 64, "swiglu"), (1, 2048, 8192, "w4a4"), (5, 2049, 8256, "w4a4"), (16, 33, 33024, "w4a4"),
+      (13, 1000, 8384, "w4a8"), (1, 2049, 8192, "w4a8")]
 
 
 @pytest.mark.parametrize("M,N,K,family", FORMS)
