@@ -54,13 +54,16 @@ def test_every_slice_kernel_is_tested(plan, family):
     assert reached == built(plan, family)
 
 
-def test_split_sizes_are_split(plan):
+def test_ring_sizes_run_on_the_ring(plan):
     t = test_gpu_slice
     for M, N, K, a8 in t.SPLIT:
         assert 0 < plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 0)[0] < N, (M, N, K)
         assert plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 1)[0] in (0, N), (M, N, K)
     for M, I, K in t.SPLIT_SWIGLU:
         assert 0 < plan_of(plan, SWIGLU, M, 2 * I, K, 0)[0] < 2 * I, (M, I, K)
+    for family in (W4A4, SWIGLU, W4A8):  # half and whole 256 x 256 tiles
+        sizes = [(M, 2 * I, K) for M, I, K in t.RING_SWIGLU] if family == SWIGLU else [c[:3] for c in t.RING if c[3] == (family == W4A8)]
+        assert [plan_of(plan, family, *c, 0)[:2] for c in sizes] == [(c[1], i) for i, c in enumerate(sizes)]
     for M, N, K, a8 in t.WHOLE:
         assert plan_of(plan, W4A8 if a8 else W4A4, M, N, K, 0)[0] == N, (M, N, K)
     for M, I, K in t.WHOLE_SWIGLU:

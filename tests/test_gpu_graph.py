@@ -21,7 +21,7 @@ def up(a):
 
 @pytest.mark.parametrize("M", [1, 4])
 def test_decode_step_graph_replays_match_eager(M):
-    # M = 1: the dot-product decode kernels; M = 4: the 16-row decode kernels
+    # one token and a small batch, both on the slice kernel
     shape = workloads.LLAMA2_7B_MLP
     H, I = shape.hidden, shape.inter
     print(f"[gpu case] graph of a decode step M={M}, LLaMA-2-7B MLP", flush=True)

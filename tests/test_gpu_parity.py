@@ -532,8 +532,7 @@ def swiglu_case(M, I, K, seed, bias=True, ldh_pad=0, sample_rows=None):
                                             (17, 160, 256, True, 0), (33, 128, 128, False, 1),
                                             (130, 352, 512, True, 8), (300, 96, 320, True, 0)])
 def test_swiglu_linear_shapes(M, I, K, bias, pad):
-    # decode kernel (M <= 16), 128 x 128 tiles (M <= 128), 256 x 128 tiles; ragged M and N,
-    # padded or odd output strides (element-wise stores)
+    # ragged M and N, padded or odd output strides (element-wise stores)
     say(f"w4a4_linear_swiglu M={M} I={I} K={K} bias={bias} ldh pad {pad}")
     og = swiglu_case(M, I, K, seed=400 + M + I + K, bias=bias, ldh_pad=pad)
     if M * I >= 2000:  # the gate values reach SiLU's flat, curved and linear parts
@@ -564,10 +563,10 @@ def test_gemm_llama2_70b_decode(M):
 
 
 def test_gemm_decode_kernel():
-    # M <= 16 runs the weight-streaming kernel: every M up to 16, ragged N (blocks of 16
-    # rows; N picks 1 to 8 blocks per workgroup), K not a multiple of the 8 waves' 64-byte
-    # steps, and K shorter than one step
-    say("w4a4_linear decode kernel: M 1..16, ragged N and K, 1-8 row blocks per workgroup")
+    # M <= 16 always runs on the slice kernel: ragged token counts up to a block of 16, ragged N
+    # (blocks of 16 weight rows, up to 8 a tile), K not a multiple of the waves' segments, and K
+    # shorter than one segment of every wave (waves without any)
+    say("w4a4_linear on slices: M 1..16, ragged N and K")
     for (M, N, K) in [(1, 8, 64), (2, 40, 128), (7, 1000, 4160), (16, 130, 3136), (11, 4097, 640),
                       (3, 8200, 256), (5, 12300, 192), (9, 16390, 128), (4, 20500, 64), (6, 24600, 128),
                       (16, 28672 + 48, 192), (13, 96, 28672)]:
@@ -575,23 +574,18 @@ def test_gemm_decode_kernel():
 
 
 def test_gemm_gemv_kernel():
-    # M <= 2 runs the dot-product kernel: whole 1 KB chunks of a row per wave load, K/2 not
-    # a multiple of 1 KB, K/2 shorter than one chunk, the largest K it takes (65536) and the
-    # first it leaves to the 16-row kernel, fewer rows than waves, and runs of more than 64
-    # rows per wave's share (more workgroups); M = 3 and 4 on 117 MB of weights, which it
-    # also took before the streaming kernel did
-    say("w4a4_linear dot-product decode kernel: M 1..4, ragged N and K")
+    # matrix-vector products on the slice kernel: fewer weight rows than a block, a long K on few
+    # tiles, more tiles than CUs, and 117 MB of weights
+    say("w4a4_linear M 1..4, few and many weight rows, short and long K")
     for (M, N, K) in [(1, 3, 64), (2, 8, 64), (1, 1000, 4160), (2, 4097, 2112), (1, 700, 65536),
                       (2, 300, 65600), (1, 2048 * 64 + 5, 64), (3, 8192, 28672), (4, 8197, 24576)]:
         gemm_case(M, N, K, seed=M * 37 + N + K, bias=(N % 2 == 1))
 
 
 def test_gemm_stream_kernel():
-    # 2 < M <= 16 on larger weights runs the LDS-streaming kernel (on a 256-CU part): ragged
-    # N (a partial last block of 16 rows), K/2 not a multiple of the 256-byte stage, 1 to 16
-    # blocks per workgroup, a single block, and runs of the 8 waves that cross one or two
-    # block boundaries (16 blocks of 2 stages); rows past M of the 16-row blocks
-    say("w4a4_linear LDS-streaming decode kernel: M 3..16, ragged N and K, runs across blocks")
+    # weight streams on the slice kernel: a partial last block of 16 weight rows, one block in
+    # all, K/2 not a multiple of a segment, one and several rounds of tiles; rows past M
+    say("w4a4_linear weight streams: M 3..16, ragged N and K")
     for (M, N, K) in [(16, 4096 * 3 + 40, 2112), (5, 16 * 256 * 16 - 16 * 7, 576), (3, 300, 65536),
                       (12, 8208, 2048), (8, 17, 16384), (16, 16, 8192), (7, 4096, 11008)]:
         gemm_case(M, N, K, seed=M * 41 + N + K, bias=(K % 3 == 0))
@@ -600,17 +594,16 @@ def test_gemm_stream_kernel():
 @pytest.mark.parametrize("M,I,K,bias", [(6, 4128, 2112, True), (9, 32, 4096, False), (11, 28672, 8256, True),
                                         (16, 11008, 4096, True)])
 def test_swiglu_stream_kernel(M, I, K, bias):
-    # the LDS-streaming kernel with SiLU: pairs of a gate and an up block of 16 rows, a
-    # single group of four blocks in all, a last workgroup with fewer pairs (LLaMA-2-7B:
-    # 688 pairs, 3 per workgroup), and runs crossing block boundaries (17 stages a block)
-    say(f"w4a4_linear_swiglu LDS-streaming decode kernel M={M} I={I} K={K} bias={bias}")
+    # weight streams with SiLU: pairs of a gate and an up block of 16 rows, two pairs in all, and
+    # a last tile with fewer pairs (LLaMA-2-7B: 688 pairs)
+    say(f"w4a4_linear_swiglu weight stream M={M} I={I} K={K} bias={bias}")
     swiglu_case(M, I, K, seed=700 + M + I + K, bias=bias)
 
 
 @pytest.mark.parametrize("M,I,K,bias", [(1, 96, 4160, True), (2, 32, 64, False), (1, 2048 * 64 + 32, 64, True),
                                         (2, 4128, 2112, True), (3, 14336, 8192, False)])
 def test_swiglu_gemv_kernel(M, I, K, bias):
-    say(f"w4a4_linear_swiglu dot-product decode kernel M={M} I={I} K={K} bias={bias}")
+    say(f"w4a4_linear_swiglu M={M} I={I} K={K} bias={bias}")
     swiglu_case(M, I, K, seed=600 + M + I + K, bias=bias)
 
 
@@ -649,19 +642,16 @@ def test_w4a8_gemm_small_shapes(M, N, K):
                                    (1, 64, 65600), (8, 8192, 28672), (3, 4096 * 3 + 40, 2112),
                                    (5, 16 * 256 * 16 - 16 * 7, 576), (8, 17, 16384), (4, 4096, 11008)])
 def test_w4a8_decode_shapes(M, N, K):
-    # M <= 16 with 8-bit activations: the dot-product kernel for one row (two from 32 MB of
-    # weights; ragged N and K, K/2 shorter than 1 KB, long runs, the largest K it takes and
-    # the first it leaves), the LDS-streaming kernel up to 8 rows (ragged N, K/2 not a
-    # multiple of its 256-byte stage, 1 to 16 blocks per workgroup, runs across block
-    # boundaries) and the 16-row kernel (1, 2 or 4 blocks of 16 rows) otherwise
+    # M <= 16 with 8-bit activations on the slice kernel: ragged N and K, K/2 shorter than a
+    # segment and not a multiple of one, few and many tiles, one block of weight rows in all
     say(f"w4a8_linear decode M={M} N={N} K={K}")
     gemm8_case(M, N, K, seed=M * 13 + N + K, bias=(M % 2 == 1))
 
 
 def test_w4a8_prefill_kernels():
-    # the ring kernels with 8-bit A blocks (128 x 256 tiles; 256 x 256 tiles from 256 such
-    # tiles on): ragged M and N, K not a multiple of a 128-k stage
-    say("w4a8_linear prefill ring kernel")
+    # prompts with 8-bit codes: slices of several shapes and the ring's 256 x 256 tiles, ragged M
+    # and N, K not a multiple of a 128-k stage
+    say("w4a8_linear prompts")
     for (M, N, K) in [(300, 390, 448), (257, 600, 320), (129, 1000, 2112), (640, 520, 1024), (2048, 300, 256),
                       (4096, 4096, 128), (4000, 4100, 320)]:
         gemm8_case(M, N, K, seed=M + N + K + 7)
@@ -971,9 +961,8 @@ def test_kv_full_sampled():
     check_kv(q, k, v, sample)
 
 
-# Each size class of the dispatch: 16 < M <= 128 (128 x 128 tiles, two K groups), fewer
-# than 256 tiles of 256 x 256 (128 x 256 tiles of 8 waves), at least 256 such tiles
-# (8-wave 256 x 256); ragged M, N and K (K % 128 == 64: a half stage)
+# Slices (one and several rounds of tiles) and, from 256 tiles of 256 x 256, the ring's large
+# tiles; ragged M, N and K (K % 128 == 64: a half stage), in every kind of store
 GEMM_CLASS_SHAPES = [(64, 130, 192), (100, 1000, 2112), (300, 390, 448), (257, 257, 128), (520, 600, 320),
                      (384, 264, 2112), (4096, 4096, 192), (4000, 4100, 320)]
 
@@ -1007,8 +996,8 @@ def test_gemm_size_classes(M, N, K):
     assert not host(wide8[:, N:]).any()
 
 
-# Operands of 2 GB and more do not fit the 31-bit buffer offsets of the ring and decode
-# kernels, and take the register-staged kernels.  The big operand repeats a few seeded rows
+# Operands of 2 GB and more do not fit the 31-bit buffer offsets of the ring kernel and run on
+# the slice kernel, whose offsets are relative to a tile.  The big operand repeats a few seeded rows
 # (built on the device), so the oracle computes the sampled outputs from those rows.  K % 128
 # == 64 takes the half stage at the end of K.
 def big_gemm_case(M, N, K, big, seed, a8=False, rows=None):
@@ -1055,21 +1044,43 @@ def big_gemm_case(M, N, K, big, seed, a8=False, rows=None):
 
 
 @pytest.mark.slow
-@pytest.mark.parametrize("M,N,K,big", [(4100, 64, (1 << 20) - 64, "a"),    # 256 x 256 register-staged tiles
-                                       (100, 4100, (1 << 20) - 64, "w"),   # 128 x 128 (M <= 128)
-                                       (8, 4100, (1 << 20) - 64, "w")])    # decode-sized M
+@pytest.mark.parametrize("M,N,K,big", [(4100, 64, (1 << 20) - 64, "a"),
+                                       (100, 4100, (1 << 20) - 64, "w"),
+                                       (8, 4100, (1 << 20) - 64, "w")])
 def test_gemm_beyond_31bit_offsets(M, N, K, big):
-    say(f"w4a4_linear M={M} N={N} K={K}: {big} operand >= 2 GB, register-staged kernel")
+    say(f"w4a4_linear M={M} N={N} K={K}: {big} operand >= 2 GB")
     big_gemm_case(M, N, K, big, seed=M + N)
 
 
 @pytest.mark.slow
-@pytest.mark.parametrize("M,N,K", [(16400, 64, (1 << 17) - 64),   # 128 x 64-deep tiles (K % 128 == 64)
-                                   (16400, 64, 1 << 17),          # 128 x 128
-                                   (16400, 1024, 1 << 17)])       # 256 x 128 (>= 512 wide tiles)
+@pytest.mark.parametrize("M,N,K", [(16400, 64, (1 << 17) - 64),   # K % 128 == 64
+                                   (16400, 64, 1 << 17),
+                                   (16400, 1024, 1 << 17)])       # several rounds of tiles
 def test_w4a8_beyond_31bit_offsets(M, N, K):
-    say(f"w4a8_linear M={M} N={N} K={K}: 8-bit codes >= 2 GB, register-staged kernel")
+    say(f"w4a8_linear M={M} N={N} K={K}: 8-bit codes >= 2 GB")
     big_gemm_case(M, N, K, "a", seed=M + N + 1, a8=True)
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("M,N,K", [(2, 65600, 65536), (1, 65664, 65472)])
+def test_swiglu_beyond_31bit_offsets(M, N, K):
+    """Gate/up weights of 2 GB and more (taken for one and two tokens): 64 rows, a block of gate
+    and one of up rows, over and over, so every 32 outputs are the same."""
+    say(f"w4a4_linear_swiglu M={M} N={N} K={K}: weights >= 2 GB")
+    rng = workloads.rng_for(M + N)
+    qa, qg, qu = rng.integers(0, 16, (M, K)), rng.integers(-7, 8, (32, K)), rng.integers(-7, 8, (32, K))
+    xa, xb = rng.uniform(0.05, 3.0, M).astype(np.float32), rng.uniform(-20.0, 0.0, M).astype(np.float32)
+    ga, ua = (rng.uniform(1e-4, 2e-3, 32).astype(np.float32) for _ in range(2))
+    rsg, rsu = qg.sum(1).astype(np.int32), qu.sum(1).astype(np.int32)
+    both = lambda g, u: dev(np.concatenate([g, u])).repeat(N // 64)
+    wq = dev(oq.pack_nibbles(np.concatenate([qg, qu]))).repeat(N // 64, 1)
+    assert wq.numel() >= 1 << 31
+    h = host(sq.w4a4_linear_swiglu(dev(oq.pack_nibbles(qa)), dev(xa), dev(xb), wq, both(ga, ua), both(rsg, rsu)))
+    del wq
+    torch.cuda.empty_cache()
+    oh, _, _ = olin.swiglu_linear(qa, xa, xb, qg, ga, rsg, qu, ua, rsu)
+    parity.assert_out_close(h[:, :32], oh)
+    np.testing.assert_array_equal(h.reshape(M, N // 64, 32), np.broadcast_to(h[:, None, :32], (M, N // 64, 32)))
 
 
 def tile_rows(M, tile=256):
@@ -1100,9 +1111,8 @@ def test_swiglu_llama2_7b_full_tiles():
                                    (5, 16 * 256 * 16 - 16 * 7, 576), (100, 1000, 2112),
                                    (2048, 4096, 11008), (4096, 4096, 192)])
 def test_gemm_deterministic(M, N, K):
-    # dot-product decode kernel (lane sums added by DPP), LDS-streaming decode kernel (the
-    # waves' partial sums of a block added in LDS), two K groups (partial sums exchanged in
-    # LDS), 128 x 256 and 256 x 256 ring tiles: two launches give the same bytes
+    # slices of four and eight waves (partial sums added in LDS), 128 x 256 and 256 x 256 ring
+    # tiles: two launches give the same bytes
     say(f"w4a4_linear determinism M={M} N={N} K={K}")
     rng = workloads.rng_for(M + N + K + 3)
     qa = rng.integers(0, 16, size=(M, K))

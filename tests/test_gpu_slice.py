@@ -88,16 +88,19 @@ SPLIT_SWIGLU = [(1000, 8224, 1088), (2377, 1728, 1600), (2697, 1568, 1408)]
 # ... and such that the ring takes whole, its last round short
 WHOLE = [(2100, 8200, 576, True)]
 WHOLE_SWIGLU = [(2100, 4128, 1088), (2600, 6144, 1088)]
+# The ring's two tiles, ragged in M, N and K (a half stage at the end)
+RING = [(2349, 1669, 448, False), (3847, 3851, 448, False), (2708, 1411, 448, True), (3883, 3841, 448, True)]
+RING_SWIGLU = [(2017, 1120, 448), (3843, 1952, 448)]
 
 
-@pytest.mark.parametrize("M,N,K,a8", SPLIT + WHOLE)
+@pytest.mark.parametrize("M,N,K,a8", SPLIT + WHOLE + RING)
 def test_ring_and_slice(M, N, K, a8):
     say(f"ring and slice on parts of one product M={M} N={N} K={K} 8-bit={a8}")
     rows = np.array([0, 1, M // 2, M - 1])
     (gemm8_case if a8 else gemm_case)(M, N, K, seed=M + N, sample_rows=rows)
 
 
-@pytest.mark.parametrize("M,I,K", SPLIT_SWIGLU + WHOLE_SWIGLU)
+@pytest.mark.parametrize("M,I,K", SPLIT_SWIGLU + WHOLE_SWIGLU + RING_SWIGLU)
 def test_ring_and_slice_swiglu(M, I, K):
     say(f"ring and slice on parts of one gate/up product M={M} I={I} K={K}")
     swiglu_case(M, I, K, seed=M + I, sample_rows=np.arange(0, M, 97))
