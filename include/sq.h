@@ -230,8 +230,10 @@ sq_status sq_w4a8_linear(const uint8_t* xq, const float* x_alpha, const float* x
  *   N          2 * I (I outputs), N % 64 == 0
  *   h          device fp16 [M, ldh], ldh >= N/2, 2-byte aligned
  * No raw-accumulator output (sq_w4a4_linear gives the accumulators of the same product).
- * Errors: SQ_ERR_NULL, SQ_ERR_SHAPE, SQ_ERR_ALIGN, SQ_ERR_ALIAS, SQ_ERR_UNSUPPORTED (sizes
- * whose byte offsets exceed 31 bits), SQ_ERR_HIP.
+ * Errors: SQ_ERR_NULL, SQ_ERR_SHAPE, SQ_ERR_ALIGN, SQ_ERR_ALIAS, SQ_ERR_UNSUPPORTED (operands
+ * of about 2^31 bytes and more: (M + 256) K/2 and (N + 256) K/2 below 2^31 - 128 are always
+ * taken; with M <= 16 only the weights count, with M <= 2 and K <= 65536 nothing is refused),
+ * SQ_ERR_HIP.
  */
 sq_status sq_w4a4_linear_swiglu(const uint8_t* xq, const float* x_alpha, const float* x_beta, int64_t M,
                                 const uint8_t* wq, const float* w_alpha, const int32_t* w_rowsum,

@@ -51,8 +51,8 @@ constexpr bool slice_has(GemmFamily f, int nb, int mb) {
 // Eight waves with one short slot each, two per SIMD, instead of four waves with two slots:
 // one wave's expansion of the codes runs under the other's products.  That pays in one round
 // of tiles where a wave has enough products (12 blocks) or the few stages of a short K are
-// mostly start and end; over a long K whole cache lines matter more, SiLU pairs gain nothing
-// and 8-bit 4 x 4 tiles lose 1 - 3 %.  Time against four waves, K = 4096 | 8192 | 11008 | 14336 |
+// mostly start and end; over a long K whole cache lines matter more, and SiLU pairs and 8-bit
+// 4 x 4 tiles gain nothing.  Time against four waves, K = 4096 | 8192 | 11008 | 14336 |
 // 28672 (geometric means over 1 - 13 products each):
 //   4-bit  1 x 1 .94 | - | 1.13 | 1.17 | -           2 x 2 .87 | 1.01 | 1.04 | 1.05 | 1.23
 //          4 x 4 .92 | .94 | .90 | .92 | 1.13        4 x 5 .94 | .98 | .94 | .96 | 1.21
@@ -108,6 +108,7 @@ constexpr bool slice_built(GemmFamily f, int nb, int mb, const SliceRing& r) {
 // x 2048] 25.4 and 23.0; [16 x 65536 x 128] 11.1 on 8 x 4 tiles, 8.0 on 4 x 2.
 constexpr double kBlockUs = 0.05, kRingStartUs = 3.0;
 constexpr bool short_k(const GemmArgs& g) { return g.K < 4096; }
+// (Terms of 0.0010 sit at the fit's lower bound: those tiles cost what their operands do.)
 struct SliceCost {
   float base, mem_tb, tile, ceil, alone, l2_tb;
   float shape[kSliceShapes];  // us per 128 k of a round, in the order of kSliceShape
@@ -174,7 +175,7 @@ inline bool ring_fits(GemmFamily f, const GemmArgs& g, bool large) {
   const int64_t kb = g.K / 2, ka = f == kW4A8 ? g.K : kb;
   return (g.M + t.bm) * ka + 128 < (int64_t{1} << 31) && (g.N + t.bn) * kb + 64 < (int64_t{1} << 31);
 }
-// At least as many 256 x 256 tiles as a 256-CU part has CUs.
+// At least as many 256 x 256 tiles as the part the line was measured on has CUs.
 inline bool ring_large(GemmFamily f, const GemmArgs& g) { return ring_tiles(f, g, true) >= 256; }
 
 // Rounds of the ring kernel's tiles; the last one costs nearly as much as a full one.
@@ -239,7 +240,7 @@ struct GemmPlan {
 // rounds of its tiles and the slice kernel on the rest, where the last round would leave CUs
 // idle; the ring wherever the others are not at least 7 % faster by the estimates, which is
 // about their error.
-// Measured on MI355X (us, against the ring alone): W4A8 [1024 x 22016 x 4096] 104 vs 117 (256
+// Measured on MI355X (us, three rotating weight sets, against the ring alone): W4A8 [1024 x 22016 x 4096] 104 vs 117 (256
 // tiles and 5632 rows of slices instead of two rounds for 344 tiles), [1536 x 22016 x 4096]
 // 138 vs 181, [1100 x 8192 x 28672] 306 vs 446; W4A4 [2300 x 4096 x 14336] 125 vs 176, [2100 x
 // 8192 x 8192] 120 vs 168; with SiLU [1300 x 22016 x 4096] 106 vs 140.

@@ -23,8 +23,10 @@ namespace sq {
 // workspace: N = 4096 and 24 tokens are 256 tiles of 16 x 32.
 //   * Operands go from global memory straight into the wave's own ring slots
 //     (buffer_load ... lds), SEG contiguous bytes of each of 16 rows per block, every
-//     fragment is one ds_read_b128 (positions swizzled by row: no bank conflicts), and each
-//     lane's 16 packed bytes expand into the operands of two v_mfma_i32_16x16x64_i8.
+//     fragment is one ds_read_b128 (positions swizzled by row: no bank conflicts in 128-byte
+//     rows; 64-byte rows keep some, 0.81e6 cycles against 0.32e6 LDS instructions in [300 x 11008]
+//     x [4096 x 11008]), and each lane's 16 packed bytes expand into the operands of two
+//     v_mfma_i32_16x16x64_i8.
 //   * A stage's fragments are read into registers and its slot is refilled before the
 //     products start, so every slot is in flight while the wave multiplies.
 //   * Rows past M or N and bytes past K are out of the buffer ranges and land as zeros.
@@ -32,15 +34,17 @@ namespace sq {
 //     index is divided by a multiplication, and the epilogue's scales are fetched behind them
 //     (1.0 - 1.3 us less before the first products: [48 x 4096] x [28672 x 4096] with SiLU 14.0
 //     to 13.2, [300 x 11008] x [4096 x 11008] 18.3 to 17.3).
-// Measured on MI355X (us, three rotating weight sets; before: 128 x 128 and 128 x 256 ring
-// tiles from 17 tokens, streaming and dot-product kernels below):
+// Measured on MI355X (us, three rotating weight sets, the smaller of them from the Infinity Cache;
+// before: 128 x 128 and 128 x 256 ring tiles from 17 tokens, kernels of their own for fewer):
 //   4-bit  [77 x 28672] x [8192 x 28672]   32.3 vs 116     [300 x 11008] x [4096 x 11008]  18.3 vs 63.4
 //          [16 x 28672] x [8192 x 28672]   21.8 vs 26.8    [128 x 4096] x [4096 x 4096]     6.2 vs 21.7
 //          [1 x 8192] x [57344 x 8192]     40.2 vs 43.5    [1 x 4096] x [4096 x 4096]       3.6 vs 5.4
 //   8-bit  [24 x 14336] x [4096 x 14336]    9.5 vs 98.2    [8 x 8192] x [57344 x 8192]     45.4 vs 78.1
 //   SiLU   [48 x 4096] x [28672 x 4096]    14.0 vs 20.7    [1 x 4096] x [22016 x 4096]      9.1 vs 11.0
-// At 1 to 16 tokens that is 5.5 - 5.9 TB/s of weights.  Operands of 2 GB and more: 8 x 4
-// tiles against the register-staged kernel they replace, 4-bit [2048 x 22016 x 4096] 230 vs
+// On weights of 100 MB and more, 1 to 16 tokens read 5.2 - 5.8 TB/s; smaller ones take less (1 x
+// 4096 x 4096 2.3).  Where the weights come from memory, several rounds of one-slot tiles lose
+// more than the ring does: [160 x 4096] x [28672 x 4096] 36.8 against 32.7, from the cache 29.5
+// against 31.7.  Operands of 2 GB and more: 8 x 4 tiles against the kernel they replaced, 4-bit [2048 x 22016 x 4096] 230 vs
 // 283, [4096 x 64 x 131072] 239 vs 1861; 8-bit 288 vs 413, 287 vs 1217.
 template <int NB, int MB, int W, int NS, int SEG, bool A8>
 struct Slice {
@@ -64,8 +68,8 @@ struct Slice {
   static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
-// Position of 16-byte chunk c of row r (of 16) in a block whose rows are RB bytes: the 16
-// lanes of one LDS read (16 rows, one chunk column) fall on distinct banks.
+// Position of 16-byte chunk c of row r (of 16) in a block whose rows are RB bytes, so that the 16
+// lanes of one chunk column fall on distinct banks.
 template <int RB>
 __device__ __forceinline__ uint32_t slice_pos(int r, int c) {
   constexpr int SH = RB == 64 ? 2 : RB == 128 ? 1 : 0;

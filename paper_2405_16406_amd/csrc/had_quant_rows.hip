@@ -38,7 +38,7 @@
 // workgroups, and the row-pair kernel at every row count):
 //                          1 row   16 rows  512 rows  1024 rows  2048 rows  4096 rows
 //   H_172 (x) S_64   now    4.4      4.7      7.8      (14.1)     (25.3)     (48.7)
-//                    pair   9.0      9.6     10.8       13.1       20.5       33.4
+//                    pair   9.0      9.6     10.8       12.9       19.8       32.8
 //   H_28 (x) S_512   now    3.8      4.1      6.9       10.0       18.0       38.1
 //                    before 4.9      5.2      9.4       14.4       23.3       44.3
 //   H_28 (x) S_1024  now    6.3      6.6     12.0       20.8       44.0       82.3

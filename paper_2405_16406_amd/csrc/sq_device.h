@@ -63,7 +63,7 @@ __device__ __forceinline__ int sym_code(float v, float inv) {
 // values in its two results, in every lane).  The six dependent ds_bpermute of a shuffle
 // reduction cost a few hundred cycles more, which kernels of one or two rows per workgroup do
 // not hide.  On MI355X (us): unrotated quantization of 1 x 4096 2.20 vs 2.66, 16 x 8192 2.90 vs
-// 3.23, 4096 x 4096 8.88 vs 9.25; with R4 1 x 11008 8.55 vs 8.93, 4096 x 14336 44.6 vs 45.7.
+// 3.23, 4096 x 4096 8.88 vs 9.25.
 template <typename Op>
 __device__ __forceinline__ uint32_t wave_all(uint32_t v, Op op) {
   const auto dpp = [](uint32_t u, auto ctrl) {

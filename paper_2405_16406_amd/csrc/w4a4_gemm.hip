@@ -559,9 +559,9 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t stream) {
                 div_magic(static_cast<uint32_t>(tm)), g);
 }
 
-// Gate/up products are taken where the byte offsets of the kernels they were first built on
-// fit 31 bits: one or two tokens always (K <= 65536), decode sizes by the rows of a
-// workgroup past N, others by the ring tile's rows past M and N.
+// Gate/up products the entry point takes: sq.h refuses operands of about 2^31 bytes and more (one
+// or two tokens with K <= 65536 are always taken, up to 16 tokens count the weights alone).  The
+// slice kernel itself has no such limit.
 bool swiglu_covered(const GemmArgs& g, int cus) {
   constexpr int64_t lim = int64_t{1} << 31;
   const int64_t kb = g.K / 2;
