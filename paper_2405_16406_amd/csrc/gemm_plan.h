@@ -240,10 +240,10 @@ struct GemmPlan {
 // rounds of its tiles and the slice kernel on the rest, where the last round would leave CUs
 // idle; the ring wherever the others are not at least 7 % faster by the estimates, which is
 // about their error.
-// Measured on MI355X (us, three rotating weight sets, against the ring alone): W4A8 [1024 x 22016 x 4096] 104 vs 117 (256
-// tiles and 5632 rows of slices instead of two rounds for 344 tiles), [1536 x 22016 x 4096]
-// 138 vs 181, [1100 x 8192 x 28672] 306 vs 446; W4A4 [2300 x 4096 x 14336] 125 vs 176, [2100 x
-// 8192 x 8192] 120 vs 168; with SiLU [1300 x 22016 x 4096] 106 vs 140.
+// Measured on MI355X (us, three rotating weight sets, against the ring alone): W4A8 [1024 x 22016 x
+// 4096] 104 vs 117 (256 tiles and 5632 rows of slices instead of two rounds for 344 tiles), [1536 x
+// 22016 x 4096] 138 vs 181, [1100 x 8192 x 28672] 306 vs 446; W4A4 [2300 x 4096 x 14336] 125 vs 176,
+// [2100 x 8192 x 8192] 120 vs 168; with SiLU [1300 x 22016 x 4096] 106 vs 140.
 inline GemmPlan plan_gemm(GemmFamily f, const GemmArgs& g, int cus) {
   constexpr double kClear = 0.93;
   GemmPlan best{0, false, plan_slice(f, g, cus)};

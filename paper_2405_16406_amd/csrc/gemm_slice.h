@@ -44,8 +44,8 @@ namespace sq {
 // On weights of 100 MB and more, 1 to 16 tokens read 5.2 - 5.8 TB/s; smaller ones take less (1 x
 // 4096 x 4096 2.3).  Where the weights come from memory, several rounds of one-slot tiles lose
 // more than the ring does: [160 x 4096] x [28672 x 4096] 36.8 against 32.7, from the cache 29.5
-// against 31.7.  Operands of 2 GB and more: 8 x 4 tiles against the kernel they replaced, 4-bit [2048 x 22016 x 4096] 230 vs
-// 283, [4096 x 64 x 131072] 239 vs 1861; 8-bit 288 vs 413, 287 vs 1217.
+// against 31.7.  Operands of 2 GB and more: 8 x 4 tiles against the kernel they replaced, 4-bit
+// [2048 x 22016 x 4096] 230 vs 283, [4096 x 64 x 131072] 239 vs 1861; 8-bit 288 vs 413, 287 vs 1217.
 template <int NB, int MB, int W, int NS, int SEG, bool A8>
 struct Slice {
   static constexpr int THREADS = 64 * W;
